@@ -139,6 +139,7 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   }
   s.ev_off = c.take<int64_t>(E + 1);
   s.row_cnt = c.take<uint32_t>(SR);
+  s.row_x = reinterpret_cast<const float*>(s.row_cnt);
   s.row_off = c.take<uint32_t>(SR + 1);
   s.bins = c.take<RowBins>(SR);
   s.row_bin = c.take<uint32_t>(SR + 1);
@@ -294,9 +295,10 @@ const char* geometry_error(const tpc_geometry* g) {
 }
 
 // The constants every kernel receives, from a checked geometry and params.
-void fill_constants(DevConst& k, const tpc_geometry* g, const tpc_params* p) {
+void fill_constants(DevConst& k, RowTable& x, const tpc_geometry* g, const tpc_params* p) {
   std::memset(&k, 0, sizeof(k));
-  for (int r = 0; r < kRows; ++r) k.row_x[r] = g->row_x[r];
+  std::memset(&x, 0, sizeof(x));
+  for (int r = 0; r < kRows; ++r) x.x[r] = g->row_x[r];
   k.tanh_half = g->tan_half_angle;
   k.z_max = g->z_max;
   k.sy0 = g->sigma_y0;
@@ -348,6 +350,7 @@ thread_local std::string g_init_error;
 
 struct tpc_ctx {
   DevConst k;
+  RowTable x;
   tpc_params p;
   tpc_geometry g;
   hipStream_t stream;
@@ -433,10 +436,10 @@ int build_grid(tpc_ctx* ctx, SlotHost& h) {
   for (int e = 0; e < h.n_events; ++e) max_ev = std::max<int64_t>(max_ev, h.ev_off[e + 1] - h.ev_off[e]);
   const unsigned chunks = (unsigned)((max_ev + kCountChunkHost - 1) / kCountChunkHost);
   k_count<<<dim3(chunks, h.n_events), 256, 0, st>>>(s);
-  k_row_layout<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s, ctx->k);
+  k_row_layout<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s, ctx->k, ctx->x);
   scan_u32(st, s.row_off, nullptr, SR, s.scan_b, nullptr);
   scan_u32(st, s.row_bin, nullptr, SR, s.scan_b, nullptr);
-  k_row_finish<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s, ctx->p.n_min_chain, ctx->p.n_min_track);
+  k_row_finish<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s, ctx->x, ctx->p.n_min_chain, ctx->p.n_min_track);
   scan_u32(st, s.tl_base, nullptr, s.n_sectors, s.scan_b, nullptr);
   scan_u32(st, s.tk_base, nullptr, s.n_sectors, s.scan_b, nullptr);
   k_scatter<<<grid_stride_blocks(h.n, 256), 256, 0, st>>>(s);
@@ -528,7 +531,7 @@ int finalize(tpc_ctx* ctx, SlotHost& h) {
   scan_u32(st, s.out_ntk, s.out_count, s.cap_tk, s.scan_b, s.out_count + 1);
   k_event_hits<<<(h.n_events + 1 + 255) / 256, 256, 0, st>>>(s);
   // 8 lanes per track (tracks <= clusters / 10 + sectors)
-  k_write_out<<<grid_stride_blocks(std::max<int64_t>(1, h.n / 50) * 8, 256, 16384), 256, 0, st>>>(s, ctx->k);
+  k_write_out<<<grid_stride_blocks(std::max<int64_t>(1, h.n / 50) * 8, 256, 16384), 256, 0, st>>>(s);
   mark(ctx, 7);
   TPC_LAUNCHED();
   h.state = 4;
@@ -659,7 +662,7 @@ int tpc_init_geometry(tpc_ctx** out, const tpc_geometry* g, const tpc_params* p,
   ctx->stream = reinterpret_cast<hipStream_t>(hip_stream);
   ctx->ws = reinterpret_cast<uint8_t*>(dev_workspace);
   ctx->ws_bytes = ws_bytes;
-  fill_constants(ctx->k, g, p);
+  fill_constants(ctx->k, ctx->x, g, p);
   Carver c{ctx->ws, 0, false};
   ctx->slots.resize(p->max_slots);
   for (int i = 0; i < p->max_slots; ++i) carve_slot(c, *p, ctx->slots[i].d, &ctx->slots[i]);
@@ -1384,7 +1387,7 @@ extern "C" int tpc_track_event_noalloc(const tpc_geometry* g, const tpc_params* 
   ctx->stream = reinterpret_cast<hipStream_t>(hip_stream);
   ctx->ws = sd.ptr;
   ctx->ws_bytes = kStaticScratchBytes;
-  fill_constants(ctx->k, g, &q);
+  fill_constants(ctx->k, ctx->x, g, &q);
   SlotHost& h = ctx->slots[0];
   Carver c{sd.ptr, 0, false};
   carve_slot(c, q, h.d, &h);

@@ -66,10 +66,10 @@ __device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_
   const Hit x = S.hit[h];
   const uint32_t* bod = S.bin_off + Bd.base;
   const uint32_t* bou = S.bin_off + Bu.base;
-  const float xr = K.row_x[row];
-  const float rho_d = K.row_x[row - 1] / xr;
-  const float rho_u = K.row_x[row + 1] / xr;
-  const float f = (xr - K.row_x[row - 1]) / (K.row_x[row + 1] - K.row_x[row - 1]);
+  const float xd = S.row_x[row - 1], xr = S.row_x[row], xu = S.row_x[row + 1];
+  const float rho_d = xd / xr;
+  const float rho_u = xu / xr;
+  const float f = (xr - xd) / (xu - xd);
   const float W = K.nf_w;
   const float yh = x.y, zh = x.z;
   const float ypu = yh * rho_u, zpu = zh * rho_u;
@@ -85,29 +85,29 @@ __device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_
     const float sy = sigma_y(K, zh), sz = sigma_z(K, zh);
     const float wy = 1.0f / (1.5f * (sy * sy));
     const float wz = 1.0f / (1.5f * (sz * sz));
-    for_window_hits<WB>(Bd, bod, S.hit, ypd, zpd, W, W, [&](uint32_t d, const Hit& xd) {
-      if (!(fabsf(xd.y - ypd) <= W && fabsf(xd.z - zpd) <= W)) return;
+    for_window_hits<WB>(Bd, bod, S.hit, ypd, zpd, W, W, [&](uint32_t d, const Hit& hd) {
+      if (!(fabsf(hd.y - ypd) <= W && fabsf(hd.z - zpd) <= W)) return;
       if (nu <= kNfCand) {
         // the listed up hits, WB records per memory round trip
         for (int k0 = 0; k0 < nu; k0 += WB) {
           uint32_t uu[WB];
-          Hit xu[WB];
+          Hit hu[WB];
 #pragma unroll
           for (int v = 0; v < WB; ++v)
             if (k0 + v < nu) {
               uu[v] = my[(k0 + v) * kNfThreads];
-              xu[v] = S.hit[uu[v]];
+              hu[v] = S.hit[uu[v]];
             }
 #pragma unroll
           for (int v = 0; v < WB; ++v)
             if (k0 + v < nu)
-              best.offer(nf_metric(xd.y, xd.z, xu[v].y, xu[v].z, yh, zh, f, wy, wz), xd.id,
-                         xu[v].id, (int32_t)d, (int32_t)uu[v]);
+              best.offer(nf_metric(hd.y, hd.z, hu[v].y, hu[v].z, yh, zh, f, wy, wz), hd.id,
+                         hu[v].id, (int32_t)d, (int32_t)uu[v]);
         }
       } else {
         for_window_hits<WB>(Bu, bou, S.hit, ypu, zpu, W, W, [&](uint32_t u, const Hit& c) {
           if (!(fabsf(c.y - ypu) <= W && fabsf(c.z - zpu) <= W)) return;
-          best.offer(nf_metric(xd.y, xd.z, c.y, c.z, yh, zh, f, wy, wz), xd.id, c.id,
+          best.offer(nf_metric(hd.y, hd.z, c.y, c.z, yh, zh, f, wy, wz), hd.id, c.id,
                      (int32_t)d, (int32_t)u);
         });
       }

@@ -188,21 +188,17 @@ void launch_track_write(int rb, int blocks, hipStream_t st, const Slot& S, int g
   }
 }
 
-struct PassOut {
-  Helix<double> st;
-  int rlast, jlast, n;
-  double chi2;
-};
-
-// One inward pass over the owned hits own[jmin .. n-1] (ascending rows):
-// state reset to the outermost hit with the prior covariance, transport row
-// by row, update with every owned hit (no gate).  A failed transport ends
-// the pass.  Memory reads are issued ahead of their use.
-__device__ __forceinline__ void refit_pass(const Slot& S, const DevConst& K, const int32_t* own,
-                           const uint8_t* own_row, int n, int jmin, double s0, double t0,
-                           double q0, PassOut& o) {
+// The inward walk of one pass over the owned hits own[jmin .. n-1]
+// (ascending rows): state reset to the outermost hit with the prior
+// covariance, transport row by row, update with every owned hit (no gate).
+// True: st is the state after the update with own[jmin], where the walk
+// ends.  False: a transport failed below the hit jlast, the last one
+// updated; st is of no use then.  Memory reads are issued ahead of their use.
+__device__ __forceinline__ bool refit_walk(const Slot& S, const DevConst& K, const RowRadii& R, const int32_t* own,
+                                           const uint8_t* own_row, int n, int jmin, double s0,
+                                           double t0, double q0, Helix<double>& st, double& chi2,
+                                           int& jlast) {
   const Hit xo = S.hit[own[n - 1]];
-  Helix<double> st;
   st.y = (double)xo.y;
   st.z = (double)xo.z;
   st.s = s0;
@@ -213,45 +209,52 @@ __device__ __forceinline__ void refit_pass(const Slot& S, const DevConst& K, con
     const double sy = sy0 + sy1z * fabs(st.z), sz = sz0 + sz1z * fabs(st.z);
     reset_cov(st, sy * sy, sz * sz, (double)K.cs0, (double)K.ct0, (double)K.cq0);
   }
-  o.st = st;
-  o.rlast = own_row[n - 1];
-  o.jlast = n - 1;
-  o.n = 1;
-  o.chi2 = 0.0;
+  chi2 = 0.0;
+  jlast = n - 1;
   const double smax = K.smax, chi2max = K.chi2max;
   // row-synchronous walk (every lane moves one row per iteration).  Every
   // memory read of a step is issued at its top and used after the
   // transport: the radius of the next row, the record of the next owned
   // hit (own[j]) and the list entry after it (own[j - 1]); indices clamped
   // into [jmin, n) and row 0 so the reads stay inside the lists.
+  const int r_out = own_row[n - 1];
   int j = n - 2;
   int rn = j >= jmin ? (int)own_row[j] : -1;
   int32_t pn = own[max(j, jmin)];
-  const int rstop = j >= jmin ? (int)own_row[jmin] : o.rlast;
-  double x_hi = (double)K.row_x[o.rlast];
-  float x_next = K.row_x[max(o.rlast - 1, 0)];
-  for (int r = o.rlast - 1; r >= rstop; --r) {
+  const int rstop = j >= jmin ? (int)own_row[jmin] : r_out;
+  double x_hi = (double)R.x[r_out];
+  float x_next = R.x[max(r_out - 1, 0)];
+  for (int r = r_out - 1; r >= rstop; --r) {
     const double x_lo = (double)x_next;
-    x_next = K.row_x[max(r - 1, 0)];
+    x_next = R.x[max(r - 1, 0)];
     const Hit xh = S.hit[pn];
     const int ja = max(j - 1, jmin);
     const int32_t p_after = own[ja];
     const int r_after = own_row[ja];
-    if (!transport(st, x_lo - x_hi, K.bd, smax, K.kkd, K.m2d)) break;
+    if (!transport(st, x_lo - x_hi, K.bd, smax, K.kkd, K.m2d)) return false;
     x_hi = x_lo;
     if (r != rn) continue;
     const double sy = sy0 + sy1z * fabs(st.z), sz = sz0 + sz1z * fabs(st.z);
     double ch = 0.0;
     kalman_update(st, (double)xh.y, (double)xh.z, sy * sy, sz * sz, chi2max, smax, false, &ch);
-    o.chi2 = o.chi2 + ch;
-    o.n += 1;
-    o.st = st;
-    o.rlast = r;
-    o.jlast = j;
+    chi2 = chi2 + ch;
+    jlast = j;
     --j;
     pn = p_after;
     rn = j >= jmin ? r_after : -1;
   }
+  return true;
+}
+
+// One pass: a failed transport ends it at the last hit updated.  The state
+// there is not kept on the way (20 doubles copied at every update, a seventh
+// of a step's instructions, for the few tracks that need it): the walk is
+// made again down to that hit, by the same arithmetic, and so ends there.
+__device__ __forceinline__ void refit_pass(const Slot& S, const DevConst& K, const RowRadii& R, const int32_t* own,
+                                           const uint8_t* own_row, int n, int& jmin, double s0,
+                                           double t0, double q0, Helix<double>& st, double& chi2) {
+  int jlast;
+  while (!refit_walk(S, K, R, own, own_row, n, jmin, s0, t0, q0, st, chi2, jlast)) jmin = jlast;
 }
 
 // a7: refit of each track over its owned hits, in double, three inward
@@ -262,6 +265,8 @@ __device__ __forceinline__ void refit_pass(const Slot& S, const DevConst& K, con
 // at the innermost fitted hit; its cluster is marked for the canonical
 // ordering.
 __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int ns) {
+  __shared__ RowRadii R;
+  load_radii(S, R);
   const uint32_t tk0 = S.tk_base[g0];
   // tracks past the region were not written (capacity error raised)
   const uint32_t total = min(S.range_cnt[1], S.tk_base[g0 + ns] - tk0);
@@ -289,36 +294,42 @@ __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int n
     const int rin_tl = S.tl_info[(size_t)T * 4 + 1];
     const float* sv = S.tl_state + (size_t)T * 5;
     const double smax = K.smax;
-    PassOut o;
+    // the three passes: jmin, the innermost hit a pass reached, only grows
+    Helix<double> st;
+    double chi2 = 0.0;
+    int jmin = 0;
     bool ok = true;
-    {
-      const double sin_ = sv[2], tin = sv[3], qin = sv[4];
-      const double s0 = sin_ + (K.bd * qin) * ((double)K.row_x[ro] - (double)K.row_x[rin_tl]);
-      if (!(fabs(s0) <= smax)) ok = false;
-      else refit_pass(S, K, own, own_row, n, 0, s0, tin, qin, o);
+    double sin_ = sv[2], tin = sv[3], qin = sv[4];
+    int rin = rin_tl;
+    for (int pass = 0; ok && pass < 3; ++pass) {
+      const double s0 = sin_ + (K.bd * qin) * ((double)R.x[ro] - (double)R.x[rin]);
+      if (!(fabs(s0) <= smax)) {
+        ok = false;
+        break;
+      }
+      refit_pass(S, K, R, own, own_row, n, jmin, s0, tin, qin, st, chi2);
+      sin_ = st.s;
+      tin = st.t;
+      qin = st.q;
+      rin = own_row[jmin];
     }
-    for (int pass = 1; ok && pass < 3; ++pass) {
-      const double sin_ = o.st.s, tin = o.st.t, qin = o.st.q;
-      const double s0 = sin_ + (K.bd * qin) * ((double)K.row_x[ro] - (double)K.row_x[o.rlast]);
-      if (!(fabs(s0) <= smax)) ok = false;
-      else refit_pass(S, K, own, own_row, n, o.jlast, s0, tin, qin, o);
-    }
-    if (!ok || o.n < K.n_min_track) continue;
+    const int nfitted = n - jmin;
+    if (!ok || nfitted < K.n_min_track) continue;
     out[0] = 1;
-    out[1] = o.n;
-    out[2] = o.rlast;
+    out[1] = nfitted;
+    out[2] = rin;
     out[3] = ro;
     double* par = S.tk_par + (size_t)k * 5;
-    par[0] = o.st.y;
-    par[1] = o.st.z;
-    par[2] = o.st.s;
-    par[3] = o.st.t;
-    par[4] = o.st.q;
+    par[0] = st.y;
+    par[1] = st.z;
+    par[2] = st.s;
+    par[3] = st.t;
+    par[4] = st.q;
     double* cov = S.tk_cov + (size_t)k * 15;
 #pragma unroll
-    for (int i = 0; i < 15; ++i) cov[i] = o.st.c[i];
-    S.tk_chi2[k] = o.chi2;
-    S.tmap[S.hit[own[o.jlast]].id] = (int32_t)k;
+    for (int i = 0; i < 15; ++i) cov[i] = st.c[i];
+    S.tk_chi2[k] = chi2;
+    S.tmap[S.hit[own[jmin]].id] = (int32_t)k;
   }
   wave_add_u64(&S.stats[3], nfit);
 }

@@ -112,9 +112,9 @@ __global__ void __launch_bounds__(kCountThreads) k_count(Slot S) {
 
 // Bin layout of one row with n hits: ~bin_target hits per bin, edges at
 // least bin_min_edge, at most kBinsPerHit * max(n, 1) bins.
-__device__ RowBins make_bins(const DevConst& K, int row, bool side_c, uint32_t n) {
+__device__ RowBins make_bins(const DevConst& K, float x_row, bool side_c, uint32_t n) {
   RowBins b;
-  const float ymax = K.row_x[row] * K.tanh_half + K.medge;
+  const float ymax = x_row * K.tanh_half + K.medge;
   const float wy = 2.0f * ymax;
   const float wz = K.z_max + 2.0f * K.mz;
   b.y0 = -ymax;
@@ -144,13 +144,13 @@ __device__ RowBins make_bins(const DevConst& K, int row, bool side_c, uint32_t n
 
 // a2: per row, the bin layout (from the row's count) and the two counts
 // the scans turn into offsets: clusters -> row_off, bins -> row_bin.
-__global__ void k_row_layout(Slot S, DevConst K) {
+__global__ void k_row_layout(Slot S, DevConst K, RowTable X) {
   const int SR = S.n_sectors * kRows;
   const int stride = gridDim.x * blockDim.x;
   for (int sr = blockIdx.x * blockDim.x + threadIdx.x; sr < SR; sr += stride) {
     const uint32_t cnt = S.row_cnt[sr];
     const int g = sr / kRows, row = sr - (sr / kRows) * kRows;
-    const RowBins b = make_bins(K, row, (g % kSectorsPerEvent) >= kSectorsPerEvent / 2, cnt);
+    const RowBins b = make_bins(K, X.x[row], (g % kSectorsPerEvent) >= kSectorsPerEvent / 2, cnt);
     if (cnt > (uint32_t)kMaxRowHits) atomicAdd(&S.err[1], 1u);
     S.bins[sr] = b;
     S.row_off[sr] = cnt;
@@ -162,11 +162,12 @@ __global__ void k_row_layout(Slot S, DevConst K) {
 // for start hits / tracklets (<= n_g/n_min_chain + 1: each heads its own
 // cleaned chain of >= n_min_chain hits, and the chains are disjoint) and tracks (<= n_g/n_min_track + 1: each track owns at least
 // n_min_track hits no other track owns), as counts for the next scans.
-__global__ void k_row_finish(Slot S, int n_min_chain, int n_min_track) {
+__global__ void k_row_finish(Slot S, RowTable X, int n_min_chain, int n_min_track) {
   const int SR = S.n_sectors * kRows;
   const int stride = gridDim.x * blockDim.x;
   const int t0 = blockIdx.x * blockDim.x + threadIdx.x;
   if (t0 == 0) S.range_cnt[2] = 0;   // rows over 1024 hits, listed by the row sort
+  if (t0 < kRows) const_cast<float*>(S.row_x)[t0] = X.x[t0];   // row_cnt is done with
   for (int sr = t0; sr < SR; sr += stride) {
     S.bins[sr].base = (int32_t)S.row_bin[sr];
     S.bins[sr].first = (int32_t)S.row_off[sr];

@@ -40,7 +40,7 @@ namespace tpc {
 
 constexpr int kMaxChain = 16;    // segments of one chain (each holds >= 10 of the 159 rows)
 
-__device__ __forceinline__ double xrow(const DevConst& K, int r) { return (double)K.row_x[r]; }
+__device__ __forceinline__ double xrow(const RowRadii& R, int r) { return (double)R.x[r]; }
 
 __device__ __forceinline__ void prior_d(const DevConst& K, Helix<double>& st, double zv) {
   const double sy = (double)K.sy0 + K.sy1zd * fabs(zv);
@@ -202,6 +202,8 @@ __device__ __forceinline__ const int32_t* track_hits(const Slot& S, const tpc_tr
 
 // M1
 __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot M, MergeConst C) {
+  __shared__ RowRadii R;
+  load_radii(S, R);
   const uint32_t ntk = S.out_count[0];
   const uint32_t stride = gridDim.x * blockDim.x;
   for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
@@ -227,11 +229,11 @@ __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot 
     int64_t gn = ev0 + h[min(k, nlast)];
     int rn = k <= nlast ? (int)S.row[gn] : -1;
     int32_t h_after = h[min(k + 1, nlast)];
-    double x_lo = xrow(K, t.row_in);
-    float x_next = K.row_x[min(t.row_in + 1, kRows - 1)];
+    double x_lo = xrow(R, t.row_in);
+    float x_next = R.x[min(t.row_in + 1, kRows - 1)];
     for (int r = t.row_in + 1; r <= t.row_out; ++r) {
       const double x_hi = (double)x_next;
-      x_next = K.row_x[min(r + 1, kRows - 1)];
+      x_next = R.x[min(r + 1, kRows - 1)];
       const float hy = S.y[gn], hz = S.z[gn];
       const int64_t g_after = ev0 + h_after;
       const int r_after = S.row[g_after];
@@ -287,7 +289,7 @@ __global__ void k_mg_scatter(Slot S, MergeSlot M) {
 }
 
 // M2 for the pair (A with outer state st0, B); false if incompatible
-__device__ bool pair_chi2(const DevConst& K, const MergeConst& C, const tpc_track& A,
+__device__ bool pair_chi2(const Slot& S, const DevConst& K, const MergeConst& C, const tpc_track& A,
                           const double* op, const double* oc, const tpc_track& B, double& chi2) {
   const int dir = neighbour(A.sector, B.sector);
   if (dir == 0) return false;
@@ -303,9 +305,9 @@ __device__ bool pair_chi2(const DevConst& K, const MergeConst& C, const tpc_trac
   st.t = op[3];
   st.q = op[4];
   for (int i = 0; i < 15; ++i) st.c[i] = oc[i];
-  double x = xrow(K, A.row_out);
+  double x = (double)S.row_x[A.row_out];
   if (!turn_frame(st, x, dir, K, C)) return false;
-  if (!transport_to_x(st, x, xrow(K, B.row_in), K.bd, C.smax, C.step_max, K.kkd, K.m2d)) return false;
+  if (!transport_to_x(st, x, (double)S.row_x[B.row_in], K.bd, C.smax, C.step_max, K.kkd, K.m2d)) return false;
   double d[5], Sm[15];
   d[0] = st.y - B.par[0];
   d[1] = st.z - B.par[1];
@@ -331,7 +333,7 @@ template <bool kFinal>
 __device__ __forceinline__ void pair_eval(const Slot& S, const DevConst& K, const MergeSlot& M,
                                           const MergeConst& C, int32_t a, int32_t b) {
   double ch = 0.0;
-  const bool ok = pair_chi2(K, C, S.out_tracks[a], M.op + (size_t)a * 5,
+  const bool ok = pair_chi2(S, K, C, S.out_tracks[a], M.op + (size_t)a * 5,
                             M.oc + (size_t)a * 15, S.out_tracks[b], ch);
   const unsigned long long key = (unsigned long long)__double_as_longlong(ch);
   if (kFinal) {
@@ -526,7 +528,7 @@ struct Chain {
 // changes, which fall at different rows for different chains (a loop over
 // segments with a row loop inside would hold every lane of a wave in each
 // segment until the longest one of the wave ends).
-__device__ bool chain_pass(const Slot& S, const DevConst& K, const MergeConst& C, const Chain& ch,
+__device__ bool chain_pass(const Slot& S, const DevConst& K, const RowRadii& R, const MergeConst& C, const Chain& ch,
                            double s0, double t0, double q0, Helix<double>& out, double& chi2,
                            int& n) {
   const int64_t ev0 = ch.ev0;
@@ -561,8 +563,8 @@ __device__ bool chain_pass(const Slot& S, const DevConst& K, const MergeConst& C
   float x_next;
   auto walk_from = [&](int row) {
     r = row - 1;
-    x_hi = xrow(K, row);
-    x_next = K.row_x[max(row - 1, 0)];
+    x_hi = xrow(R, row);
+    x_next = R.x[max(row - 1, 0)];
     const int kk = max(k, 0);
     gn = ev0 + h[kk];
     rn = k >= 0 ? (int)S.row[gn] : -1;
@@ -582,7 +584,7 @@ __device__ bool chain_pass(const Slot& S, const DevConst& K, const MergeConst& C
       --j;
       const int dir = neighbour(sector, ch.sec[j]);
       sector = ch.sec[j];
-      double x = xrow(K, cur_row);
+      double x = xrow(R, cur_row);
       if (!turn_frame(st, x, dir, K, C)) return false;
       h = S.out_hits + ch.hoff[j];
       k = ch.nh[j] - 1;
@@ -590,7 +592,7 @@ __device__ bool chain_pass(const Slot& S, const DevConst& K, const MergeConst& C
       by = S.y[g];
       bz = S.z[g];
       const int rb = ch.rout[j];
-      const double d = xrow(K, rb) - x;
+      const double d = xrow(R, rb) - x;
       if (!(fabs(d) <= 1000.0)) return false;
       sub = max(1, (int)ceil(fabs(d) / C.step_max));
       dxb = d / (double)sub;
@@ -608,7 +610,7 @@ __device__ bool chain_pass(const Slot& S, const DevConst& K, const MergeConst& C
     const bool walking = sub == 0;
     if (walking) {
       const double x_lo = (double)x_next;
-      x_next = K.row_x[max(r - 1, 0)];
+      x_next = R.x[max(r - 1, 0)];
       hy = S.y[gn];
       hz = S.z[gn];
       g_after = ev0 + h_after;
@@ -647,11 +649,11 @@ __device__ bool chain_pass(const Slot& S, const DevConst& K, const MergeConst& C
 // pass resets the covariance, so only its parameters matter): through each
 // segment to its last row in equal steps of at most step_max, turning
 // frames between segments; one flat loop of steps, as the pass.
-__device__ bool carry_out(const DevConst& K, const MergeConst& C, const Chain& ch,
+__device__ bool carry_out(const DevConst& K, const RowRadii& R, const MergeConst& C, const Chain& ch,
                           Helix<double> st, double& s0, double& t0, double& q0) {
-  double x = xrow(K, ch.rin[0]);
+  double x = xrow(R, ch.rin[0]);
   int j = 0;
-  double xo = xrow(K, ch.rout[0]);
+  double xo = xrow(R, ch.rout[0]);
   double d = xo - x;
   if (!(fabs(d) <= 1000.0)) return false;
   int sub = max(1, (int)ceil(fabs(d) / C.step_max));
@@ -663,7 +665,7 @@ __device__ bool carry_out(const DevConst& K, const MergeConst& C, const Chain& c
     if (++j == ch.n) break;
     const int dir = neighbour(ch.sec[j - 1], ch.sec[j]);
     if (!turn_frame<false>(st, x, dir, K, C)) return false;
-    xo = xrow(K, ch.rout[j]);
+    xo = xrow(R, ch.rout[j]);
     d = xo - x;
     if (!(fabs(d) <= 1000.0)) return false;
     sub = max(1, (int)ceil(fabs(d) / C.step_max));
@@ -677,6 +679,8 @@ __device__ bool carry_out(const DevConst& K, const MergeConst& C, const Chain& c
 
 // M4: refit of each chain (lane per chain head)
 __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot M, MergeConst C) {
+  __shared__ RowRadii R;
+  load_radii(S, R);
   const uint32_t ntk = S.out_count[0];
   const uint32_t stride = gridDim.x * blockDim.x;
   for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
@@ -708,8 +712,8 @@ __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot 
     double chi2 = 0.0;
     int nh = 0;
     for (int pass = 0; pass < C.passes && good; ++pass) {
-      if (pass > 0) good = carry_out(K, C, ch, res, s0, t0, q0);
-      if (good) good = chain_pass(S, K, C, ch, s0, t0, q0, res, chi2, nh);
+      if (pass > 0) good = carry_out(K, R, C, ch, res, s0, t0, q0);
+      if (good) good = chain_pass(S, K, R, C, ch, s0, t0, q0, res, chi2, nh);
     }
     if (!good) continue;
     M.head_ok[a] = 1;

@@ -184,7 +184,7 @@ __global__ void k_event_hits(Slot S) {
 constexpr int kOutLanes = 8;
 constexpr int kOutBatch = 8;
 
-__global__ void k_write_out(Slot S, DevConst K) {
+__global__ void k_write_out(Slot S) {
   const uint32_t ntk = S.out_count[0];
   const uint32_t ngroups = gridDim.x * blockDim.x / kOutLanes;
   const uint32_t gid = (blockIdx.x * blockDim.x + threadIdx.x) / kOutLanes;
@@ -219,7 +219,7 @@ __global__ void k_write_out(Slot S, DevConst K) {
       o.hit_off = (int64_t)(hoff - ehoff);
       o.inner_id = (int32_t)((int64_t)gidx - ev0);
       o.start_id = (int32_t)((int64_t)S.hit[S.start_hit[T]].id - ev0);
-      o.x_ref = (double)K.row_x[ti[2]];
+      o.x_ref = (double)S.row_x[ti[2]];
       o.ndf = 2 * nh - 5;
       o.event = e;
       const double* par = S.tk_par + (size_t)k * 5;

@@ -31,7 +31,6 @@ constexpr uint16_t kNoEntry = 0xFFFFu;        // hit-list entry of a row without
 // constants handed to every kernel by value
 // ---------------------------------------------------------------------------
 struct DevConst {
-  float row_x[kRows + 1];
   float tanh_half;
   float z_max;
   float sy0, sy1, sz0, sz1;
@@ -47,6 +46,14 @@ struct DevConst {
   float bin_min_edge;
   float kk, m2;             // scattering law k^2/X0 and mass^2 (0: no scattering), float
   double kkd, m2d;          // the same in double (refit, merger)
+};
+
+// Pad-row radii, handed to the kernels that build the grid; they leave them in
+// device memory for the others (Slot::row_x).  A lane's read of a kernel
+// argument by index goes to the argument buffer, in host memory: over a
+// microsecond, more than a filter step, and longer with more waves reading.
+struct RowTable {
+  float x[kRows + 1];
 };
 
 // per (sector, row) grid description
@@ -78,7 +85,9 @@ struct Slot {
   int32_t n_sectors;        // 36 * n_events
   int64_t n;                // clusters
   // grid
-  uint32_t* row_cnt;        // [SR]
+  uint32_t* row_cnt;        // [SR] clusters of each row, until the rows are laid out
+  const float* row_x;       // [kRows] pad-row radii (in the memory of row_cnt, written after it
+                            // was last read)
   uint32_t* row_off;        // [SR+1] first sorted hit of each (sector, row)
   RowBins* bins;            // [SR]
   uint32_t* row_bin;        // [SR+1] bins per row, then the rows' first bin
@@ -179,6 +188,15 @@ __device__ __forceinline__ int32_t entry_hit(uint32_t e, uint32_t first) {
   return e == kNoEntry ? -1 : (int32_t)(first + e);
 }
 
+// the pad-row radii in LDS, for the kernels that walk the rows
+struct RowRadii {
+  float x[kRows + 1];
+};
+__device__ __forceinline__ void load_radii(const Slot& S, RowRadii& R) {
+  for (int r = threadIdx.x; r < kRows; r += blockDim.x) R.x[r] = S.row_x[r];
+  __syncthreads();
+}
+
 // ---------------------------------------------------------------------------
 // pad-row bins: monotone in y and z, identical in every kernel
 // ---------------------------------------------------------------------------
@@ -272,6 +290,57 @@ template <> __device__ __forceinline__ double fabs_(double v) { return fabs(v); 
 template <class F> __device__ __forceinline__ F sqrt_(F v);
 template <> __device__ __forceinline__ float sqrt_(float v) { return sqrtf(v); }
 template <> __device__ __forceinline__ double sqrt_(double v) { return sqrt(v); }
+// Square root, reciprocal and quotient, correctly rounded, for operands that
+// the caller knows to be well inside the exponent range: the bits of sqrtf /
+// sqrt and of the division without the scaling and special-case steps that
+// the compiler adds around them (a filter step has four of these, and its
+// lanes are bound by the number of instructions).  Zero, infinity and NaN
+// give NaN.  Goldschmidt / Newton steps on the hardware's estimate, the last
+// ones on the residual (Markstein 1990).
+//  float   5 and 3 instructions instead of 16 and 11; compared with the
+//          compiler's operations on every float in [2^-100, 2^100]: equal.
+//  double  the residual step that makes the result exact is kept, as the
+//          compiler has it: 10 instead of 18, and 7 instead of 11.
+__device__ __forceinline__ float sqrt_mid(float x) {
+  const float r = __builtin_amdgcn_rsqf(x);
+  const float g = x * r, h = 0.5f * r;
+  return fmaf(fmaf(-g, g, x), h, g);
+}
+__device__ __forceinline__ double sqrt_mid(double x) {
+  const double r = __builtin_amdgcn_rsq(x);
+  double g = x * r, h = 0.5 * r;
+  const double e = fma(-h, g, 0.5);
+  g = fma(g, e, g);
+  h = fma(h, e, h);
+  g = fma(fma(-g, g, x), h, g);
+  return fma(fma(-g, g, x), h, g);
+}
+__device__ __forceinline__ float rcp_mid(float x) {
+  const float y = __builtin_amdgcn_rcpf(x);
+  return fmaf(fmaf(-x, y, 1.0f), y, y);
+}
+__device__ __forceinline__ double rcp_mid(double x) {
+  double y = __builtin_amdgcn_rcp(x);
+  y = fma(fma(-x, y, 1.0), y, y);
+  y = fma(fma(-x, y, 1.0), y, y);
+  return fma(fma(-x, y, 1.0), y, y);
+}
+
+// True if |x| lies in [2^-100, 2^100], where the short forms hold (false for NaN).
+__device__ __forceinline__ bool mid_range(float x) {
+  const float a = fabsf(x);
+  return a >= 0x1p-100f && a <= 0x1p100f;
+}
+// Reciprocal of a residual covariance's determinant.  In float it is tested:
+// cluster errors given as tiny numbers reach the ends of the range.  In
+// double the squares of four floats stay far from them.
+__device__ __forceinline__ float rcp_det(float x) {
+  float y = rcp_mid(x);
+  if (!mid_range(x)) y = 1.0f / x;
+  return y;
+}
+__device__ __forceinline__ double rcp_det(double x) { return rcp_mid(x); }
+
 // a*b + c rounded once.  Every sum of products of the filter is a chain of
 // these in a fixed order (the CPU checker uses the same chains), so results
 // stay bit-identical with contraction switched off for everything else.
@@ -286,6 +355,11 @@ template <> __device__ __forceinline__ double fma_(double a, double b, double c)
 // Returns false, leaving the state untouched, if |sin phi| would pass smax.
 // kCov = false moves the parameters only (the same arithmetic for them),
 // for callers that discard the covariance.
+// The roots and the reciprocal are the short ones: smax is a float below 1,
+// so 1 - s1^2 >= 2^-24 and c1 >= 2^-12, D lies in [2^-12, 2] and 1 + tmid^2
+// in [1, 2^27].  (s0 alone may be past smax, as an update without a gate
+// leaves it: |s0| > 1 gives NaN here as it does in a general root; |s0| = 1
+// makes iD, and with it every entry that iD enters, NaN either way.)
 template <class F, bool kCov = true>
 __device__ __forceinline__ bool transport(Helix<F>& h, F dx, F b, F smax, F kk = F(0),
                                           F m2 = F(0)) {
@@ -294,23 +368,23 @@ __device__ __forceinline__ bool transport(Helix<F>& h, F dx, F b, F smax, F kk =
   const F s1 = fma_(bq, dx, h.s);
   if (!(fabs_(s1) <= smax)) return false;
   const F s0 = h.s;
-  const F c0 = sqrt_(fma_(-s0, s0, one));
-  const F c1 = sqrt_(fma_(-s1, s1, one));
+  const F c0 = sqrt_mid(fma_(-s0, s0, one));
+  const F c1 = sqrt_mid(fma_(-s1, s1, one));
   const F N = s0 + s1;
   const F D = c0 + c1;
   // one division: the reciprocals of D, c0 and c1 are products with
   // 1/(c0 c1 D)
   const F c01 = c0 * c1;
-  const F inv = one / (c01 * D);
+  const F inv = rcp_mid(c01 * D);
   const F iD = c01 * inv;
   const F ic0 = (c1 * D) * inv;
   const F ic1 = (c0 * D) * inv;
   const F tmid = N * iD;
-  const F chord = fabs_(dx) * sqrt_(fma_(tmid, tmid, one));
+  // chord and arc with the sign of dx
+  const F chord = dx * sqrt_mid(fma_(tmid, tmid, one));
   const F u = half * bq * chord;
   const F u2 = u * u;
-  F arc = chord * fma_(u2, fma_(u2, F(3) / F(40), one / F(6)), one);
-  if (dx < F(0)) arc = -arc;
+  const F arc = chord * fma_(u2, fma_(u2, F(3) / F(40), one / F(6)), one);
 
   // Jacobian; dz/dQ to leading order, 2 T b N dx^2 / D^3 (the mid-angle
   // cosine taken as D/2)
@@ -393,7 +467,7 @@ __device__ __forceinline__ Resid<F> resid_weights(const Helix<F>& h, F vy, F vz)
   const F s01 = h.c[1];
   const F s11 = h.c[2] + vz;
   const F det = fma_(s00, s11, -(s01 * s01));
-  const F inv = F(1) / det;
+  const F inv = rcp_det(det);
   r.w00 = s11 * inv;
   r.w01 = -s01 * inv;
   r.w11 = s00 * inv;
@@ -407,18 +481,12 @@ __device__ __forceinline__ F chi2_of(const Resid<F>& w, F ry, F rz) {
   return fma_(ry, fma_(w.w00, ry, w.w01 * rz), rz * fma_(w.w01, ry, w.w11 * rz));
 }
 
-// Kalman update with the measurement (my, mz).  gated: refuse (state
-// untouched) when chi2 > chi2max, a variance would not stay positive or
-// |sin phi| would reach smax.
+// State and covariance after the measurement with residual (ry, rz), w the
+// residual weights of this state.  gated: refuse (state untouched) when a
+// variance would not stay positive or |sin phi| would reach smax.
 template <class F>
-__device__ __forceinline__ bool kalman_update(Helix<F>& h, F my, F mz, F vy, F vz, F chi2max,
-                                              F smax, bool gated, F* chi2_out) {
-  const Resid<F> w = resid_weights(h, vy, vz);
-  const F ry = my - h.y;
-  const F rz = mz - h.z;
-  const F chi2 = chi2_of(w, ry, rz);
-  *chi2_out = chi2;
-  if (gated && !(chi2 <= chi2max)) return false;
+__device__ __forceinline__ bool kalman_apply(Helix<F>& h, const Resid<F>& w, F ry, F rz, F smax,
+                                             bool gated) {
   const F* c = h.c;
   // covariance column of each state entry with y and with z
   const F cy[5] = {c[0], c[1], c[3], c[6], c[10]};
@@ -448,6 +516,20 @@ __device__ __forceinline__ bool kalman_update(Helix<F>& h, F my, F mz, F vy, F v
   }
   h = o;
   return true;
+}
+
+// Kalman update with the measurement (my, mz).  gated: also refused when
+// chi2 > chi2max.
+template <class F>
+__device__ __forceinline__ bool kalman_update(Helix<F>& h, F my, F mz, F vy, F vz, F chi2max,
+                                              F smax, bool gated, F* chi2_out) {
+  const Resid<F> w = resid_weights(h, vy, vz);
+  const F ry = my - h.y;
+  const F rz = mz - h.z;
+  const F chi2 = chi2_of(w, ry, rz);
+  *chi2_out = chi2;
+  if (gated && !(chi2 <= chi2max)) return false;
+  return kalman_apply(h, w, ry, rz, smax, gated);
 }
 
 // Prior covariance: measurement variances in y and z at the hit, wide

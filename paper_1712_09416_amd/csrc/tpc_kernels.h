@@ -17,8 +17,8 @@ void launch_select(int rb, int blocks, hipStream_t st, const Slot& S, const DevC
 void launch_track_write(int rb, int blocks, hipStream_t st, const Slot& S, int g0, int ns);
 // stage + grid
 __global__ void k_count(Slot S);
-__global__ void k_row_layout(Slot S, DevConst K);
-__global__ void k_row_finish(Slot S, int n_min_chain, int n_min_track);
+__global__ void k_row_layout(Slot S, DevConst K, RowTable X);
+__global__ void k_row_finish(Slot S, RowTable X, int n_min_chain, int n_min_track);
 __global__ void k_scatter(Slot S);
 __global__ void k_row_sort_tiny(Slot S);
 __global__ void k_row_sort_small(Slot S);
@@ -42,7 +42,7 @@ __global__ void k_scan_small(uint32_t* data, const uint32_t* n_dev, int64_t n_ho
 __global__ void k_flags(Slot S);
 __global__ void k_order(Slot S);
 __global__ void k_event_hits(Slot S);
-__global__ void k_write_out(Slot S, DevConst K);
+__global__ void k_write_out(Slot S);
 // cross-sector merger
 __global__ void k_mg_count(Slot S, MergeSlot M);
 __global__ void k_mg_scatter(Slot S, MergeSlot M);

@@ -9,12 +9,11 @@
 namespace tpc {
 
 // Stop rules after a transport to the row at radius xr: left the sector
-// sideways, crossed the membrane, or left the drift volume.
-__device__ __forceinline__ bool inside(const DevConst& K, const Helix<float>& h, float xr, bool side_c) {
-  if (!(fabsf(h.y) <= xr * K.tanh_half + K.medge)) return false;
-  if (!(fabsf(h.z) <= K.z_max + K.mz)) return false;
-  if (side_c ? (h.z > K.mz) : (h.z < -K.mz)) return false;
-  return true;
+// sideways, left the drift volume, or crossed the membrane (zsign = -1 on
+// the A side, 1 on the C side).
+__device__ __forceinline__ bool inside(const DevConst& K, const Helix<float>& h, float xr, float zsign) {
+  return fabsf(h.y) <= xr * K.tanh_half + K.medge && fabsf(h.z) <= K.z_max + K.mz &&
+         !(zsign * h.z > K.mz);
 }
 
 // Best hit of row sr for the predicted state: inside
@@ -26,9 +25,14 @@ __device__ __forceinline__ int32_t search_row(const Slot& S, const DevConst& K, 
                                               const Helix<float>& h, float vy, float vz,
                                               unsigned& examined, Hit& out) {
   const Resid<float> w = resid_weights(h, vy, vz);
-  float wy = K.kwin * sqrtf(w.s00);
+  float ry0 = sqrt_mid(w.s00), rz0 = sqrt_mid(w.s11);
+  if (!(mid_range(fminf(w.s00, w.s11)) && mid_range(fmaxf(w.s00, w.s11)))) {
+    ry0 = sqrtf(w.s00);
+    rz0 = sqrtf(w.s11);
+  }
+  float wy = K.kwin * ry0;
   if (wy > K.wmax) wy = K.wmax;
-  float wz = K.kwin * sqrtf(w.s11);
+  float wz = K.kwin * rz0;
   if (wz > K.wmax) wz = K.wmax;
   const float yc = h.y, zc = h.z;
   int32_t best = -1;
@@ -68,6 +72,8 @@ __device__ __forceinline__ bool try_hit(const DevConst& K, Helix<float>& h, cons
 //        search; same gap rule.  The inward hits form the tracklet.
 template <int WB>
 __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
+  __shared__ RowRadii R;
+  load_radii(S, R);
   // Tracklets are ordered by (sector, row): give each XCD (blocks are
   // dispatched round-robin over the 8 XCDs) one contiguous chunk, so the
   // hits a chunk's lanes read stay in that XCD's L2.
@@ -79,24 +85,26 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
   const uint32_t chunk = (total + kXcd - 1) / kXcd;
   const uint32_t c0 = xcd * chunk;
   const uint32_t c1 = min(total, c0 + chunk);
-  unsigned visits = 0, examined = 0, done = 0, tl_hits = 0, tries = 0;
+  unsigned n_tl = 0, n_visits = 0, n_examined = 0, n_tries = 0, tl_hits = 0;
   for (uint32_t t = c0 + j * blockDim.x + threadIdx.x; t < c1; t += nbx * blockDim.x) {
-    ++done;
+    unsigned visits = 0, examined = 0, tries = 0;
     const uint32_t T = base + t;
     const int sr0 = S.start_sr[T];
     const int g = sr0 / kRows;
-    const int r0 = sr0 - g * kRows;
-    const bool side_c = (g % kSectorsPerEvent) >= kSectorsPerEvent / 2;
-    const int64_t ev0 = S.ev_off[g / kSectorsPerEvent];
+    const int gr = g * kRows;
+    const int r0 = sr0 - gr;
+    const float zsign = (g % kSectorsPerEvent) >= kSectorsPerEvent / 2 ? 1.0f : -1.0f;
     const int32_t p0 = S.start_hit[T];
     const Hit x0 = S.hit[p0];
     const Hit x1 = S.hit[x0.upc];
     const TlList hits = tl_list(S, T);
     const uint32_t first0 = S.row_off[sr0];
+    // what a tie between tracklets of equal length goes by
+    const uint32_t id0 = x0.id - (uint32_t)S.ev_off[g / kSectorsPerEvent];
 
     // radii of the start row and the next one (r0 <= 157: a start hit has
     // an up link)
-    const float x_r0 = K.row_x[r0], x_r1 = K.row_x[r0 + 1];
+    const float x_r0 = R.x[r0], x_r1 = R.x[r0 + 1];
     Helix<float> st;
     {
       const float dx = x_r1 - x_r0;
@@ -117,7 +125,7 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     block_set(blk, r0 & 7, (uint32_t)p0 - first0);
 
     // outward
-    Helix<float> last = st;
+    float l_y = st.y, l_z = st.z, l_s = st.s, l_t = st.t, l_q = st.q;   // at the last hit
     int rout = r0;
     float x_rout = x_r0;
     int32_t next = x0.upc;     // cleaned chain link of the last accepted hit
@@ -129,13 +137,13 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     // the seed has used, so no read before the loop is waited for inside it
     float x_prev = x_r0;
     float x_ahead = x_r1;
-    for (int r = r0 + 1; r < kRows; ++r) {
-      ++visits;
+    int r = r0 + 1;
+    for (; r < kRows; ++r) {
       const float xr = x_ahead;
-      x_ahead = K.row_x[min(r + 1, kRows - 1)];
+      x_ahead = R.x[min(r + 1, kRows - 1)];
       // reads independent of the state, issued before the transport: the
       // row's bin range and the hit the chain link points to
-      const RowBins rb = S.bins[g * kRows + r];
+      const RowBins rb = S.bins[gr + r];
       Hit xnext;
       if (chain && next >= 0) xnext = S.hit[next];
       if ((r & 7) == 0) {          // into the next block of rows
@@ -145,7 +153,7 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       }
       if (!transport(st, xr - x_prev, K.b, K.smax, K.kk, K.m2)) break;
       x_prev = xr;
-      if (!inside(K, st, xr, side_c)) break;
+      if (!inside(K, st, xr, zsign)) break;
       const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
       const float vy = sy * sy, vz = sz * sz;
       int32_t got = -1;
@@ -166,7 +174,11 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
         next = xg.upc;
         p_out = got;
         miss = 0;
-        last = st;
+        l_y = st.y;
+        l_z = st.z;
+        l_s = st.s;
+        l_t = st.t;
+        l_q = st.q;
         rout = r;
         x_rout = xr;
       } else if (++miss >= K.n_gap) {
@@ -174,26 +186,29 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       }
     }
     hits.store_block(cb, blk);
+    visits += (unsigned)(min(r, kRows - 1) - r0);
 
     // inward, covariance reset at the outermost hit
     const Hit xo = S.hit[p_out];
-    st = last;
     st.y = xo.y;
     st.z = xo.z;
+    st.s = l_s;
+    st.t = l_t;
+    st.q = l_q;
     {
       const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
       reset_cov(st, sy * sy, sz * sz, K.cs0, K.ct0, K.cq0);
     }
     int n = 1;
     int rin = rout;
-    last = st;
+    l_y = st.y;
+    l_z = st.z;
     miss = 0;
     // the blocks of the current row and of the one below, in registers (the
     // outward decisions, rewritten as the inward ones are taken; a block is
     // stored back only if an entry changed); the outward hit of the next
     // row down loaded one step ahead, the first hit of the row below it two
     // steps ahead
-    const int gr = g * kRows;
     cb = (rout - 1) >> 3;
     blk = hits.load_block(cb);
     uint4 blk_dn = cb > 0 ? hits.load_block(cb - 1) : block_empty();
@@ -204,14 +219,14 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     Hit xu_next;
     if (uh_next >= 0) xu_next = S.hit[uh_next];
     x_prev = x_rout;
-    x_ahead = K.row_x[max(rout - 1, 0)];
+    x_ahead = R.x[max(rout - 1, 0)];
     // wait for these reads here, once: a read still in flight at the loop's
     // entry would make the compiler wait inside every step
     asm volatile("" : "+v"(x_ahead), "+v"(f_next));
-    for (int r = rout - 1; r >= 0; --r) {
-      ++visits;
+    r = rout - 1;
+    for (; r >= 0; --r) {
       const float xr = x_ahead;
-      x_ahead = K.row_x[max(r - 1, 0)];
+      x_ahead = R.x[max(r - 1, 0)];
       const RowBins rb = S.bins[gr + r];
       const int32_t uh = uh_next;
       const Hit xu = xu_next;
@@ -224,7 +239,7 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       if (r - 2 >= r0) f_next = (uint32_t)S.row_off[gr + r - 2];
       if (!transport(st, xr - x_prev, K.b, K.smax, K.kk, K.m2)) break;
       x_prev = xr;
-      if (!inside(K, st, xr, side_c)) break;
+      if (!inside(K, st, xr, zsign)) break;
       const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
       const float vy = sy * sy, vz = sz * sz;
       int32_t got = -1;
@@ -244,7 +259,11 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       if (got >= 0) {
         ++n;
         miss = 0;
-        last = st;
+        l_y = st.y;
+        l_z = st.z;
+        l_s = st.s;
+        l_t = st.t;
+        l_q = st.q;
         rin = r;
       } else if (++miss >= K.n_gap) {
         break;
@@ -258,6 +277,11 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       }
     }
     if (dirty) hits.store_block(cb, blk);
+    visits += (unsigned)(rout - max(r, 0));
+    n_tl += 1u;
+    n_visits += visits;
+    n_examined += examined;
+    n_tries += tries;
     tl_hits += (unsigned)n;
     int32_t* info = S.tl_info + (size_t)T * 4;
     const bool valid = n >= K.n_min_tracklet;
@@ -265,7 +289,6 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     info[1] = rin;
     info[2] = rout;
     info[3] = valid ? 1 : 0;
-    const uint32_t id0 = (uint32_t)((int64_t)x0.id - ev0);
     const uint32_t w = ((uint32_t)n << 24) | (0xFFFFFFu - id0);
     S.tl_weight[T] = w;
     // a6 (ownership): every hit of a valid tracklet keeps the largest weight
@@ -293,17 +316,17 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       }
     }
     float* sv = S.tl_state + (size_t)T * 5;
-    sv[0] = last.y;
-    sv[1] = last.z;
-    sv[2] = last.s;
-    sv[3] = last.t;
-    sv[4] = last.q;
+    sv[0] = l_y;
+    sv[1] = l_z;
+    sv[2] = l_s;
+    sv[3] = l_t;
+    sv[4] = l_q;
   }
-  wave_add_u64(&S.stats[0], done);
-  wave_add_u64(&S.stats[1], visits);
-  wave_add_u64(&S.stats[2], examined);
+  wave_add_u64(&S.stats[0], n_tl);
+  wave_add_u64(&S.stats[1], n_visits);
+  wave_add_u64(&S.stats[2], n_examined);
   wave_add_u64(&S.stats[6], tl_hits);
-  wave_add_u64(&S.stats[7], tries);
+  wave_add_u64(&S.stats[7], n_tries);
 }
 
 void launch_tracklets(int wb, int blocks, int threads, hipStream_t st, const Slot& S,
