@@ -489,8 +489,10 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   const int64_t n_range = range_clusters(h, g0, ns);
   const int64_t tl_bound = std::min<int64_t>(s.cap_tl, n_range / ctx->p.n_min_chain + ns);
   const int tl_block = ctx->p.tl_block;
-  const int nb_lane =
-      std::max(8, grid_stride_blocks(tl_bound, tl_block, 16384 * 64 / tl_block) / 8 * 8);
+  // a wave per 64 tracklets, and enough waves to spread a few over the chip
+  const int nb_lane = std::max(
+      std::max(8, grid_stride_blocks(tl_bound, tl_block, 16384 * 64 / tl_block) / 8 * 8),
+      std::min(grid_stride_blocks(tl_bound * 64, tl_block), (int)kTrackletWaves * 64 / tl_block));
   // a multiple of 8 blocks: each XCD walks its chunk of the tracklets
   const int nb_sel = (grid_stride_blocks(tl_bound, 256, 4096) + 7) / 8 * 8;
   // a lane per hit of the range (the grid from the host bound; the kernel
@@ -514,7 +516,10 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   // four waves per block: a block's waves go to the four SIMDs of one CU,
   // so the few hundred working waves of an event do not share SIMDs
   // a multiple of 8 blocks: each XCD strides over its chunk of the tracks
-  const int nb_ref = (grid_stride_blocks(std::max<int64_t>(1, tl_bound / 4), 256, 1024) + 7) / 8 * 8;
+  const int64_t tk_bound = std::max<int64_t>(1, tl_bound / 4);
+  const int nb_ref = (std::max(grid_stride_blocks(tk_bound, 256, 1024),
+                               std::min(grid_stride_blocks(tk_bound * 64, 256), (int)kRefitWaves / 4)) +
+                      7) / 8 * 8;
   k_refit<<<nb_ref, 256, 0, st>>>(s, ctx->k, g0, ns);
   if (marks) mark(ctx, 6);
   TPC_LAUNCHED();

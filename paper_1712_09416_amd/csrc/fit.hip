@@ -280,8 +280,11 @@ __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int n
   const uint32_t c0 = min(total, xcd * chunk);
   const uint32_t c1 = min(total, c0 + chunk);
   unsigned nfit = 0;
-  for (uint32_t t = c0 + jb * blockDim.x + threadIdx.x; t < c1; t += nbx * blockDim.x) {
-    ++nfit;
+  const LaneGroup lg = lane_group(total, min(kRefitWaves, gridDim.x * (blockDim.x >> 6)));
+  const uint32_t waves = blockDim.x >> 6;
+  for (uint32_t t = c0 + (jb * waves + (threadIdx.x >> 6)) * lg.per + lg.index; t < c1;
+       t += nbx * waves * lg.per) {
+    if (lg.first) ++nfit;
     const uint32_t k = tk0 + t;
     const int32_t T = S.tk_tracklet[k];
     const int n = S.tk_nown[k];
@@ -314,7 +317,7 @@ __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int n
       rin = own_row[jmin];
     }
     const int nfitted = n - jmin;
-    if (!ok || nfitted < K.n_min_track) continue;
+    if (!ok || nfitted < K.n_min_track || !lg.first) continue;
     out[0] = 1;
     out[1] = nfitted;
     out[2] = rin;

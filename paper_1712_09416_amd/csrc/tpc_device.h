@@ -278,6 +278,30 @@ __device__ __forceinline__ void wave_add_u64(unsigned long long* dst, unsigned l
   if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, v);
 }
 
+// How a wave's lanes are dealt to `total` items (tracklets, tracks): a lane
+// an item where there are many, a group of lanes an item where there are few,
+// so that these spread over the idle SIMDs: a wave's step costs what its
+// costliest item needs (a search, a second update, the slowest of 64 reads).
+// A group's lanes all do the item's work (same addresses, one line read) and
+// the first one writes: waves of one or four active lanes issue at half the
+// rate of full ones, measured at four to a compute unit.
+// per: items of a wave, the fewest (a power of two) that give no more than
+// `most` waves.
+struct LaneGroup {
+  uint32_t per, index;      // items per wave; this lane's item in the wave
+  bool first;               // first lane of its group
+};
+__device__ __forceinline__ LaneGroup lane_group(uint32_t total, uint32_t most) {
+  uint32_t sh = 6;          // log2 of the lanes of an item
+  while (sh > 0u && (total + (64u >> sh) - 1u) / (64u >> sh) > most) --sh;
+  const uint32_t lane = threadIdx.x & 63u;
+  LaneGroup g;
+  g.per = 64u >> sh;
+  g.index = lane >> sh;
+  g.first = (lane & ((1u << sh) - 1u)) == 0u;
+  return g;
+}
+
 template <class F>
 struct Helix {
   F y, z, s, t, q;

@@ -11,6 +11,12 @@ namespace tpc {
 // rb = hit-list rows read per round trip (4, 8, 16)
 void launch_neighbours(int wb, int blocks, hipStream_t st, const Slot& S, const DevConst& K, int g0,
                        int ns);
+// waves that few tracklets / tracks are spread over: measured best of 512,
+// 1024, 2048, 4096 (tracklets, us, 32 pp events: 824, 753, 714, 770; one
+// peripheral event: 809, 762, 755, 845; tracks: 334, 328, 611, 761; 354, 325,
+// 566, 838, where two of the fp64 waves to a SIMD already share its issue)
+constexpr uint32_t kTrackletWaves = 2048;
+constexpr uint32_t kRefitWaves = 1024;
 void launch_tracklets(int wb, int blocks, int threads, hipStream_t st, const Slot& S,
                       const DevConst& K, int g0);
 void launch_select(int rb, int blocks, hipStream_t st, const Slot& S, const DevConst& K, int g0);

@@ -86,7 +86,10 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
   const uint32_t c0 = xcd * chunk;
   const uint32_t c1 = min(total, c0 + chunk);
   unsigned n_tl = 0, n_visits = 0, n_examined = 0, n_tries = 0, tl_hits = 0;
-  for (uint32_t t = c0 + j * blockDim.x + threadIdx.x; t < c1; t += nbx * blockDim.x) {
+  const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
+  const uint32_t waves = blockDim.x >> 6;
+  const uint32_t t0 = c0 + (j * waves + (threadIdx.x >> 6)) * lg.per + lg.index;
+  for (uint32_t t = t0; t < c1; t += nbx * waves * lg.per) {
     unsigned visits = 0, examined = 0, tries = 0;
     const uint32_t T = base + t;
     const int sr0 = S.start_sr[T];
@@ -278,6 +281,7 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     }
     if (dirty) hits.store_block(cb, blk);
     visits += (unsigned)(rout - max(r, 0));
+    if (!lg.first) continue;         // one lane of the tracklet's group writes
     n_tl += 1u;
     n_visits += visits;
     n_examined += examined;
