@@ -142,8 +142,9 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   s.row_x = reinterpret_cast<const float*>(s.row_cnt);
   s.row_off = c.take<uint32_t>(SR + 1);
   s.bins = c.take<RowBins>(SR);
-  s.row_bin = c.take<uint32_t>(SR + 1);
-  // a row of n hits has at most kBinsPerHit * max(n, 1) bins, plus one end entry
+  s.ev_tot = c.take<uint32_t>(SR + 1);
+  // a row of n hits has at most kBinsPerHit * max(n, 1) bins, plus one end entry;
+  // every row has room for that many (make_bins)
   s.bin_off = c.take<uint32_t>(kBinsPerHit * (N + SR) + SR + 1);
   s.rank = c.take<uint32_t>(N);
   s.hit = c.take<Hit>(N);
@@ -429,23 +430,20 @@ int build_grid(tpc_ctx* ctx, SlotHost& h) {
   Slot& s = h.d;
   hipStream_t st = ctx->stream;
   const int64_t SR = (int64_t)s.n_sectors * kRows;
-  k_zero_u32<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s.row_cnt, SR);
-  k_zero_u32<<<1, 64, 0, st>>>(s.err, 4);
-  k_zero_u32<<<1, 64, 0, st>>>(reinterpret_cast<uint32_t*>(s.stats), 16);
+  k_grid_begin<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s);
   int64_t max_ev = 1;
   for (int e = 0; e < h.n_events; ++e) max_ev = std::max<int64_t>(max_ev, h.ev_off[e + 1] - h.ev_off[e]);
   const unsigned chunks = (unsigned)((max_ev + kCountChunkHost - 1) / kCountChunkHost);
   k_count<<<dim3(chunks, h.n_events), 256, 0, st>>>(s);
-  k_row_layout<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s, ctx->k, ctx->x);
-  scan_u32(st, s.row_off, nullptr, SR, s.scan_b, nullptr);
-  scan_u32(st, s.row_bin, nullptr, SR, s.scan_b, nullptr);
-  k_row_finish<<<grid_stride_blocks(SR, 256), 256, 0, st>>>(s, ctx->x, ctx->p.n_min_chain, ctx->p.n_min_track);
-  scan_u32(st, s.tl_base, nullptr, s.n_sectors, s.scan_b, nullptr);
-  scan_u32(st, s.tk_base, nullptr, s.n_sectors, s.scan_b, nullptr);
-  k_scatter<<<grid_stride_blocks(h.n, 256), 256, 0, st>>>(s);
-  k_row_sort_tiny<<<(unsigned)SR, 64, 0, st>>>(s);
-  k_row_sort_small<<<(unsigned)SR, 256, 0, st>>>(s);
-  k_row_sort_large<<<64, 256, 0, st>>>(s);
+  if (h.n_events > 1)
+    k_rows<true><<<h.n_events, kRowThreadsLaunch, 0, st>>>(s, ctx->x, ctx->p.n_min_chain,
+                                                           ctx->p.n_min_track);
+  k_rows<false><<<h.n_events, kRowThreadsLaunch, 0, st>>>(s, ctx->x, ctx->p.n_min_chain,
+                                                          ctx->p.n_min_track);
+  const int64_t flat = (h.n + kCountChunkHost - 1) / kCountChunkHost;
+  k_scatter<<<(unsigned)std::max<int64_t>(8, (flat + 7) / 8 * 8), 256, 0, st>>>(s);
+  k_row_sort<<<(unsigned)((SR + 3) / 4), 256, 0, st>>>(s, ctx->k);
+  k_row_sort_large<<<64, 256, 0, st>>>(s, ctx->k);
   TPC_LAUNCHED();
   h.state = 2;
   return TPC_OK;
@@ -505,7 +503,7 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   k_clean_rows<<<nb_rows, 256, 0, st>>>(s, g0, ns, ctx->p.n_min_chain);
   scan_u32(st, s.row_nstart + (size_t)g0 * kRows, nullptr, (int64_t)ns * kRows, s.scan_b,
            s.range_cnt + 0, false);
-  k_start_write<<<nb_rows, 256, 0, st>>>(s, g0, ns, ctx->p.n_min_chain);
+  k_start_write<<<nb_rows, 256, 0, st>>>(s, g0, ns);
   if (marks) mark(ctx, 3);
   launch_tracklets(ctx->p.win_batch, nb_lane, ctx->p.tl_block, st, s, ctx->k, g0);
   if (marks) mark(ctx, 4);
@@ -529,12 +527,12 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
 int finalize(tpc_ctx* ctx, SlotHost& h) {
   Slot& s = h.d;
   hipStream_t st = ctx->stream;
-  const int nbn = grid_stride_blocks(h.n, 256);
-  k_flags<<<nbn, 256, 0, st>>>(s);
-  scan_u32(st, s.scan_a, nullptr, h.n, s.scan_b, nullptr);
-  k_order<<<std::max(nbn, (h.n_events + 256) / 256), 256, 0, st>>>(s);
-  scan_u32(st, s.out_ntk, s.out_count, s.cap_tk, s.scan_b, s.out_count + 1);
-  k_event_hits<<<(h.n_events + 1 + 255) / 256, 256, 0, st>>>(s);
+  // stretches of whole tiles, at most kOrderBlocks of them
+  const int64_t tiles = std::max<int64_t>(1, (h.n + kOrderTile - 1) / kOrderTile);
+  const int64_t chunk = (tiles + kOrderBlocks - 1) / kOrderBlocks * kOrderTile;
+  const unsigned nbo = (unsigned)std::max<int64_t>(1, (h.n + chunk - 1) / chunk);
+  k_out_count<<<nbo, 256, 0, st>>>(s, chunk);
+  k_out_order<<<nbo, 256, 0, st>>>(s, chunk);
   // 8 lanes per track (tracks <= clusters / 10 + sectors)
   k_write_out<<<grid_stride_blocks(std::max<int64_t>(1, h.n / 50) * 8, 256, 16384), 256, 0, st>>>(s);
   mark(ctx, 7);

@@ -181,7 +181,7 @@ __global__ void __launch_bounds__(256) k_clean_rows(Slot S, int g0, int ns, int 
         int32_t uc, dc;
         start = is_start(S, h, n_min_chain, uc, dc);
         S.hit[h].upc = uc;
-        S.dnc[h] = dc;
+        S.dnc[h] = start ? kStartHit : dc;
         S.weight[h] = 0u;
       }
       count += (uint32_t)__popcll(__ballot(start));
@@ -190,10 +190,10 @@ __global__ void __launch_bounds__(256) k_clean_rows(Slot S, int g0, int ns, int 
   }
 }
 
-// a4: write the start hits in (sector, row, position) order at the offsets
-// given by the scan of the per-row counts over the launched sector range.
-// One wave per row, as in k_clean_rows.
-__global__ void __launch_bounds__(256) k_start_write(Slot S, int g0, int ns, int n_min_chain) {
+// a4: write the start hits (marked by k_clean_rows) in (sector, row, position)
+// order at the offsets given by the scan of the per-row counts over the
+// launched sector range.  One wave per row, as in k_clean_rows.
+__global__ void __launch_bounds__(256) k_start_write(Slot S, int g0, int ns) {
   const int lane = threadIdx.x & 63;
   const int nwaves = (int)(gridDim.x * blockDim.x / 64);
   const int nr = ns * kRows;
@@ -204,11 +204,7 @@ __global__ void __launch_bounds__(256) k_start_write(Slot S, int g0, int ns, int
     uint32_t out = S.tl_base[g0] + S.row_nstart[sr];
     for (uint32_t base = h0; base < h1; base += 64) {
       const uint32_t h = base + lane;
-      bool start = false;
-      if (h < h1) {
-        int32_t uc, dc;
-        start = is_start(S, h, n_min_chain, uc, dc);
-      }
+      const bool start = h < h1 && S.dnc[h] == kStartHit;
       const unsigned long long m = __ballot(start);
       if (start) {
         const uint32_t k = out + (uint32_t)__popcll(m & below);

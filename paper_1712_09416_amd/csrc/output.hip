@@ -1,8 +1,8 @@
 // Output: tracks in canonical order (event, cluster ID of the innermost hit)
 // with their hit lists (cluster IDs of the event, ascending pad row).
 // The order is obtained without a sort: the refit marks each track's
-// innermost cluster; an exclusive scan over the clusters of the slot gives
-// every track its position.
+// innermost cluster; running counts over the clusters of the slot give every
+// track its position and its first hit.
 #include "tpc_device.h"
 #include "tpc_kernels.h"
 
@@ -150,31 +150,110 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_apply(const uint32_t* in, c
   }
 }
 
-__global__ void k_flags(Slot S) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < S.n; i += stride)
-    S.scan_a[i] = S.tmap[i] >= 0 ? 1u : 0u;
-}
-
-// Canonical position of every track, its hit count, per-event track ranges.
-__global__ void k_order(Slot S) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  for (int64_t i = t0; i < S.n; i += stride) {
-    const int32_t k = S.tmap[i];
-    if (k < 0) continue;
-    const uint32_t pos = S.scan_a[i];
-    S.out_order[pos] = k;
-    S.out_ntk[pos] = (uint32_t)S.tk_info[(size_t)k * 4 + 1];
+// Canonical order.  The refit marked each track's innermost cluster (tmap);
+// blocks take a stretch of `chunk` clusters each (a multiple of kOrderTile).
+// First the tracks and hits of every stretch:
+__global__ void __launch_bounds__(256) k_out_count(Slot S, int64_t chunk) {
+  const int64_t c0 = (int64_t)blockIdx.x * chunk;
+  const int64_t c1 = min(S.n, c0 + chunk);
+  uint32_t nt = 0, nh = 0;
+  for (int64_t i = c0 + (int64_t)threadIdx.x * 4; i < c1; i += kOrderTile) {
+    int32_t k[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) k[u] = i + u < c1 ? S.tmap[i + u] : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (k[u] >= 0) {
+        ++nt;
+        nh += (uint32_t)S.tk_info[(size_t)k[u] * 4 + 1];
+      }
   }
-  if (t0 <= S.n_events) S.ev_track_off[t0] = S.scan_a[S.ev_off[t0]];
-  if (t0 == 0) S.out_count[0] = S.scan_a[S.n];
+  uint32_t ex;
+  const uint32_t tt = block_scan256(nt, &ex), th = block_scan256(nh, &ex);
+  if (threadIdx.x == 0) {
+    S.scan_a[2 * blockIdx.x] = tt;
+    S.scan_a[2 * blockIdx.x + 1] = th;
+  }
 }
 
-// Per-event hit ranges (after the scan of the hit counts).
-__global__ void k_event_hits(Slot S) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e <= S.n_events) S.ev_hit_off[e] = S.out_ntk[S.ev_track_off[e]];
+// Then each track's position and first hit, and the per-event ranges: a block
+// adds up the stretches before its own (at most kOrderBlocks) and scans its
+// stretch tile by tile.  Counts, positions, hit offsets and event ranges were
+// nine launches (two scans of three among them), most of a small event's
+// output.
+__global__ void __launch_bounds__(256) k_out_order(Slot S, int64_t chunk) {
+  const int64_t c0 = (int64_t)blockIdx.x * chunk;
+  const int64_t c1 = min(S.n, c0 + chunk);
+  uint32_t bt = 0, bh = 0;             // tracks and hits before the stretch
+  {
+    uint32_t nt = 0, nh = 0;
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 256) {
+      nt += S.scan_a[2 * i];
+      nh += S.scan_a[2 * i + 1];
+    }
+    uint32_t ex;
+    bt = block_scan256(nt, &ex);
+    bh = block_scan256(nh, &ex);
+  }
+  // the first event starting in the stretch
+  int e = 0;
+  for (int hi = S.n_events + 1; e < hi;) {
+    const int mid = (e + hi) >> 1;
+    if (S.ev_off[mid] < c0) e = mid + 1; else hi = mid;
+  }
+  for (int64_t i0 = c0; i0 < c1; i0 += kOrderTile) {
+    const int64_t i = i0 + (int64_t)threadIdx.x * 4;
+    int32_t k[4];
+    uint32_t nh[4], nt = 0, sh = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) k[u] = i + u < c1 ? S.tmap[i + u] : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      nh[u] = k[u] >= 0 ? (uint32_t)S.tk_info[(size_t)k[u] * 4 + 1] : 0u;
+      nt += k[u] >= 0 ? 1u : 0u;
+      sh += nh[u];
+    }
+    uint32_t pt, ph;
+    const uint32_t tt = block_scan256(nt, &pt), th = block_scan256(sh, &ph);
+    // events starting in the tile: the counts before their first cluster
+    for (; e <= S.n_events; ++e) {
+      const int64_t b = S.ev_off[e];
+      if (b >= i0 + kOrderTile || b >= c1) break;
+      if (b >= i && b < i + 4) {
+        uint32_t t = bt + pt, q = bh + ph;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (i + u < b) {
+            t += k[u] >= 0 ? 1u : 0u;
+            q += nh[u];
+          }
+        S.ev_track_off[e] = t;
+        S.ev_hit_off[e] = q;
+      }
+    }
+    uint32_t t = bt + pt, q = bh + ph;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (k[u] >= 0) {
+        S.out_order[t] = k[u];
+        S.out_ntk[t] = q;
+        ++t;
+        q += nh[u];
+      }
+    bt += tt;
+    bh += th;
+  }
+  if (blockIdx.x == gridDim.x - 1) {
+    // the end, and events without clusters there
+    for (int i = e + (int)threadIdx.x; i <= S.n_events; i += 256) {
+      S.ev_track_off[i] = bt;
+      S.ev_hit_off[i] = bh;
+    }
+    if (threadIdx.x == 0) {
+      S.out_count[0] = bt;
+      S.out_count[1] = bh;
+    }
+  }
 }
 
 // Track records and hit lists (hit offsets relative to the event).  A group

@@ -24,6 +24,7 @@ constexpr int kSectorsPerEvent = 36;
 constexpr int kMaxRowHits = 4096;         // LDS sort capacity of one pad row
 constexpr int kBinsPerHit = 2;            // a row has at most this many bins per hit
 constexpr uint32_t kNoHit = 0xFFFFFFFFu;
+constexpr int32_t kStartHit = -2;         // down link of a start hit
 constexpr int kRowBlocks = (kRows + 7) / 8;   // a tracklet's hit list in blocks of 8 rows
 constexpr uint16_t kNoEntry = 0xFFFFu;        // hit-list entry of a row without hit
 
@@ -90,7 +91,7 @@ struct Slot {
                             // was last read)
   uint32_t* row_off;        // [SR+1] first sorted hit of each (sector, row)
   RowBins* bins;            // [SR]
-  uint32_t* row_bin;        // [SR+1] bins per row, then the rows' first bin
+  uint32_t* ev_tot;         // [4 E] per event: hits, tracklet and track region entries, spare
   uint32_t* bin_off;        // [2 (n + SR) + SR + 1] per row: its bins' first hits, then the end
   uint32_t* rank;           // [n]
   Hit* hit;                 // [n] sorted by (sector, row, bin, id)
@@ -98,7 +99,7 @@ struct Slot {
   // links (sorted-hit indices, -1 none); the cleaned up-link lives in hit[].upc
   int32_t* up;
   int32_t* dn;
-  int32_t* dnc;
+  int32_t* dnc;             // cleaned down link; kStartHit for a start hit (which has none)
   // per-sector regions (used by per-sector launches; contiguous for a range)
   uint32_t* tl_base;        // [S+1] tracklet region of each sector
   uint32_t* tk_base;        // [S+1] track region of each sector
@@ -125,10 +126,10 @@ struct Slot {
   double* tk_chi2;          // [tk capacity]
   // canonical order
   int32_t* tmap;            // [n] per global cluster: temp track whose innermost hit it is
-  uint32_t* scan_a;         // [n+1] scratch for the device scans
+  uint32_t* scan_a;         // [n+1] scratch: the output order's counts per stretch of clusters
   uint32_t* scan_b;         // [block partials]
   uint32_t* out_count;      // [2]: tracks, hits of the slot
-  uint32_t* out_ntk;        // [tk capacity+1] hit counts in canonical order, then offsets
+  uint32_t* out_ntk;        // [tk capacity+1] first hit of each track, in canonical order
   int32_t* out_order;       // [tk capacity] temporary track of each canonical position
   tpc_track* out_tracks;    // [tk capacity]
   int32_t* out_hits;        // [n]

@@ -23,15 +23,15 @@ void launch_select(int rb, int blocks, hipStream_t st, const Slot& S, const DevC
 void launch_track_write(int rb, int blocks, hipStream_t st, const Slot& S, int g0, int ns);
 // stage + grid
 __global__ void k_count(Slot S);
-__global__ void k_row_layout(Slot S, DevConst K, RowTable X);
-__global__ void k_row_finish(Slot S, RowTable X, int n_min_chain, int n_min_track);
+__global__ void k_grid_begin(Slot S);
+template <bool kTotals>
+__global__ void k_rows(Slot S, RowTable X, int n_min_chain, int n_min_track);
 __global__ void k_scatter(Slot S);
-__global__ void k_row_sort_tiny(Slot S);
-__global__ void k_row_sort_small(Slot S);
-__global__ void k_row_sort_large(Slot S);
+__global__ void k_row_sort(Slot S, DevConst K);
+__global__ void k_row_sort_large(Slot S, DevConst K);
 // cellular automaton
 __global__ void k_clean_rows(Slot S, int g0, int ns, int n_min_chain);
-__global__ void k_start_write(Slot S, int g0, int ns, int n_min_chain);
+__global__ void k_start_write(Slot S, int g0, int ns);
 // Kalman filter
 __global__ void k_refit(Slot S, DevConst K, int g0, int ns);
 // output
@@ -41,13 +41,15 @@ __global__ void k_scan_partials(uint32_t* partial, int nb, uint32_t* out, const 
                                 int64_t n_host, uint32_t* total_out, int write_end);
 __global__ void k_scan_apply(const uint32_t* in, const uint32_t* n_dev, int64_t n_host,
                              const uint32_t* partial, uint32_t* out);
+constexpr int kRowThreadsLaunch = 1024;   // threads of k_rows
 constexpr int kSmallPerThread = 16;
 constexpr int64_t kSmallScanMax = 1024 * kSmallPerThread;
 __global__ void k_scan_small(uint32_t* data, const uint32_t* n_dev, int64_t n_host,
                              uint32_t* total_out, int write_end);
-__global__ void k_flags(Slot S);
-__global__ void k_order(Slot S);
-__global__ void k_event_hits(Slot S);
+constexpr int kOrderBlocks = 2048;
+constexpr int kOrderTile = 1024;    // clusters a block of the output order takes at a time
+__global__ void k_out_count(Slot S, int64_t chunk);
+__global__ void k_out_order(Slot S, int64_t chunk);
 __global__ void k_write_out(Slot S);
 // cross-sector merger
 __global__ void k_mg_count(Slot S, MergeSlot M);
