@@ -491,8 +491,9 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   const int nb_lane = std::max(
       std::max(8, grid_stride_blocks(tl_bound, tl_block, 16384 * 64 / tl_block) / 8 * 8),
       std::min(grid_stride_blocks(tl_bound * 64, tl_block), (int)kTrackletWaves * 64 / tl_block));
-  // a multiple of 8 blocks: each XCD walks its chunk of the tracklets
-  const int nb_sel = (grid_stride_blocks(tl_bound, 256, 4096) + 7) / 8 * 8;
+  // 32 lanes a tracklet; a multiple of 8 blocks: each XCD walks its chunk of
+  // the tracklets
+  const int nb_sel = (grid_stride_blocks(tl_bound * 32, 256, 2048) + 7) / 8 * 8;
   // a lane per hit of the range (the grid from the host bound; the kernel
   // strides over the device count)
   launch_neighbours(ctx->p.win_batch, grid_stride_blocks(n_range, 256, 65536) / 8 * 8 + 8, st, s,
@@ -507,9 +508,8 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   if (marks) mark(ctx, 3);
   launch_tracklets(ctx->p.win_batch, nb_lane, ctx->p.tl_block, st, s, ctx->k, g0);
   if (marks) mark(ctx, 4);
-  launch_select(ctx->p.row_batch, nb_sel, st, s, ctx->k, g0);
-  scan_u32(st, s.tl_sel, s.range_cnt + 0, tl_bound, s.scan_b, s.range_cnt + 1, false);
-  launch_track_write(ctx->p.row_batch, nb_sel, st, s, g0, ns);
+  k_select<<<nb_sel, 256, 0, st>>>(s, ctx->k, g0);
+  k_track_write<<<nb_sel, 256, 0, st>>>(s, g0, ns);
   if (marks) mark(ctx, 5);
   // four waves per block: a block's waves go to the four SIMDs of one CU,
   // so the few hundred working waves of an event do not share SIMDs

@@ -15,177 +15,235 @@ __device__ __forceinline__ int wave_max(int v) {
   return v;
 }
 
-// Rows are walked RB at a time (a tuning knob): the hit-list entries of a
-// batch are loaded together, then the weights of their hits, so a batch
-// costs two memory round trips instead of two per row.
-
-// hv[u] = the tracklet's hit in row r0+u if that row is inside [rin, rout]
-// of an active lane, else -1 (rows outside are not read); gr = the
-// tracklet's sector times the rows per sector.
-template <int RB>
-__device__ __forceinline__ void load_row_batch(const Slot& S, const TlList& hits, int gr, int r0,
-                                               bool active, int rin, int rout,
-                                               int32_t (&hv)[RB]) {
-  uint32_t e[RB], f[RB];
-#pragma unroll
-  for (int u = 0; u < RB; ++u) {
-    const int r = r0 + u;
-    const bool in = active && r >= rin && r <= rout;
-    e[u] = in ? hits.at(r) : (uint32_t)kNoEntry;
-    f[u] = in ? (uint32_t)S.row_off[gr + r] : 0u;
-  }
-#pragma unroll
-  for (int u = 0; u < RB; ++u) hv[u] = entry_hit(e[u], f[u]);
-}
-
-template <int RB>
-__device__ __forceinline__ void load_weights(const Slot& S, const int32_t (&hv)[RB],
-                                             uint32_t (&wv)[RB]) {
-#pragma unroll
-  for (int u = 0; u < RB; ++u) wv[u] = hv[u] >= 0 ? S.weight[hv[u]] : 0u;
-}
-
-// a6: a valid tracklet becomes a track if it owns (holds the maximal weight
-// of) at least n_min_track of its hits.  Writes 1/0 per tracklet of the
-// range; the scan of these flags places the tracks.
-// Lane per tracklet; a wave walks the rows its 64 consecutive tracklets
-// span together, so each row's hit-list reads are contiguous (tile layout).
-// The tracklets are in sector order: each XCD (blocks are dispatched
-// round-robin over the 8; the grid is a multiple of 8) walks a contiguous
-// chunk of them, a whole number of waves, so a sector's hit lists and
-// weights are read through one XCD's L2.  Wave-aligned start of this
-// wave's first group of 64, the chunk's end, and the stride.
-struct XcdChunk {
-  uint32_t first, end, stride;
+// a6: selection.  A valid tracklet becomes a track if it owns (holds the
+// maximal weight of) at least n_min_track of its hits.
+// Few tracklets (up to kSelSparse): 32 lanes a tracklet, each with a block of
+// 8 rows of its hit list, so a tracklet costs four memory round trips
+// (record, list block, rows' first hits, weights); a lane walking its
+// tracklet's rows takes 40, which few tracklets do not hide (a pp event 24 us,
+// now 5; a peripheral event 27, now 10).  Many: a lane a tracklet, the wave
+// walking the rows its 64 consecutive tracklets span together, so that each
+// row's lists and weights are read side by side (a central event 64 us
+// against 103 with 32 lanes a tracklet, 64 events 0.48 against 1.62 ms).
+// The tracks' lists are written 32 lanes a tracklet either way (five in six
+// tracklets are not selected: 47 against 62 us and 0.60 against 0.79 ms).
+// Blocks take chunks of consecutive tracklets (in sector order), the chunks
+// of one XCD (blocks are dispatched round-robin over the 8) contiguous, so a
+// sector's hit lists and weights are read through one XCD's L2.
+constexpr uint32_t kSelLanes = 32;
+constexpr uint32_t kSelThreads = 256;
+constexpr uint32_t kSelRound = kSelThreads / kSelLanes;     // tracklets of a block's round
+constexpr uint32_t kSelSparse = 65536;
+constexpr int kSelRows = 8;                                 // rows a lane reads together
+static_assert(kRowBlocks <= (int)kSelLanes, "a lane per block of a hit list");
+struct SelChunk {
+  uint32_t size, index;      // index past the last chunk: nothing to do
 };
-__device__ __forceinline__ XcdChunk xcd_chunk(uint32_t total) {
-  constexpr uint32_t kXcd = 8;
-  const uint32_t xcd = blockIdx.x % kXcd, jb = blockIdx.x / kXcd;
-  const uint32_t nbx = gridDim.x / kXcd;
-  const uint32_t chunk = ((total + kXcd - 1) / kXcd + 63u) & ~63u;
-  const uint32_t c0 = min(total, xcd * chunk);
-  XcdChunk x;
-  x.first = c0 + ((jb * blockDim.x + threadIdx.x) & ~63u);
-  x.end = min(total, c0 + chunk);
-  x.stride = nbx * blockDim.x;
-  return x;
+__device__ __forceinline__ SelChunk sel_chunk(uint32_t total) {
+  SelChunk c;
+  const uint32_t per = (total + gridDim.x - 1) / gridDim.x;
+  const uint32_t whole = total > kSelSparse ? kSelThreads : kSelRound;   // a block's round
+  c.size = max(whole, (per + whole - 1) / whole * whole);
+  const uint32_t chunks = (total + c.size - 1) / c.size;
+  const uint32_t of_xcd = max(1u, (chunks + 7u) / 8u), j = blockIdx.x / 8u;
+  c.index = j < of_xcd ? blockIdx.x % 8u * of_xcd + j : 0xFFFFFFFFu;
+  return c;
 }
 
-template <int RB>
-__global__ void __launch_bounds__(256) k_select(Slot S, DevConst K, int g0) {
+// The hits that tracklet T owns in the lane's block of 8 rows: a bit per row,
+// the hits in hv.  info: its record (row_in, row_out used).
+__device__ __forceinline__ uint32_t owned_rows(const Slot& S, uint32_t T, int4 info, uint32_t b,
+                                               int32_t (&hv)[8]) {
+  const int rin = info.y, rout = info.z;
+  const int r0 = (int)b * 8;
+  uint32_t own = 0;
+  if (r0 <= rout && r0 + 7 >= rin) {
+    const uint32_t w = S.tl_weight[T];
+    const int gr = S.start_sr[T] / kRows * kRows;
+    const uint4 v = tl_list(S, T).load_block((int)b);
+    uint32_t first[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) first[u] = S.row_off[gr + min(r0 + u, kRows - 1)];
+    uint32_t wv[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int r = r0 + u;
+      hv[u] = r >= rin && r <= rout ? entry_hit(block_get(v, u), first[u]) : -1;
+      wv[u] = hv[u] >= 0 ? S.weight[hv[u]] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) own |= hv[u] >= 0 && wv[u] == w ? 1u << u : 0u;
+  }
+  return own;
+}
+
+// Hits that the lane's tracklet T owns (0 if it is not valid), the wave's
+// tracklets walked together row by row: the entries of kSelRows rows are read
+// together, then the weights of their hits.
+__device__ __forceinline__ uint32_t owned_by_lane(const Slot& S, uint32_t T, int4 info) {
+  const bool valid = info.w != 0;
+  const int rin = valid ? info.y : kRows, rout = valid ? info.z : -1;
+  const uint32_t w = valid ? S.tl_weight[T] : 0u;
+  const int gr = valid ? S.start_sr[T] / kRows * kRows : 0;
+  const int lo = wave_min(rin), hi = wave_max(rout);
+  const TlList hits = tl_list(S, T);
+  uint32_t n = 0;
+  for (int r0 = lo; r0 <= hi; r0 += kSelRows) {
+    uint32_t e[kSelRows], f[kSelRows];
+#pragma unroll
+    for (int u = 0; u < kSelRows; ++u) {
+      const int r = r0 + u;
+      const bool in = r >= rin && r <= rout;
+      e[u] = in ? hits.at(r) : (uint32_t)kNoEntry;
+      f[u] = in ? (uint32_t)S.row_off[gr + r] : 0u;
+    }
+    uint32_t wv[kSelRows];
+#pragma unroll
+    for (int u = 0; u < kSelRows; ++u)
+      wv[u] = e[u] != kNoEntry ? S.weight[entry_hit(e[u], f[u])] : 0u;
+#pragma unroll
+    for (int u = 0; u < kSelRows; ++u) n += e[u] != kNoEntry && wv[u] == w ? 1u : 0u;
+  }
+  return n;
+}
+
+// Per tracklet of the range the number of hits it owns if it is selected,
+// else 0; the first one of a chunk also holds the chunk's selected tracklets
+// (above the lowest 8 bits), which place the tracks.
+__global__ void __launch_bounds__(kSelThreads) k_select(Slot S, DevConst K, int g0) {
+  __shared__ uint32_t selected;
   const uint32_t total = S.range_cnt[0];
   const uint32_t base = S.tl_base[g0];
-  const uint32_t lane = threadIdx.x & 63;
-  const XcdChunk xc = xcd_chunk(total);
-  for (uint32_t tb = xc.first; tb < xc.end; tb += xc.stride) {
-    const uint32_t t = tb + lane;
-    const uint32_t T = base + t;
-    bool valid = false;
-    int rin = 1, rout = 0;
-    uint32_t w = 0;
-    int gr = 0;
-    if (t < total) {
-      const int32_t* info = S.tl_info + (size_t)T * 4;
-      valid = info[3] != 0;
-      if (valid) {
-        rin = info[1];
-        rout = info[2];
-        w = S.tl_weight[T];
-        gr = S.start_sr[T] / kRows * kRows;
-      }
+  const SelChunk c = sel_chunk(total);
+  if (c.index >= (total + c.size - 1) / c.size) return;
+  const uint32_t t0 = c.index * c.size, t1 = min(total, t0 + c.size);
+  if (threadIdx.x == 0) selected = 0;
+  __syncthreads();
+  const uint32_t b = threadIdx.x % kSelLanes;
+  uint32_t mine = 0, first = 0;
+  if (total > kSelSparse) {
+    for (uint32_t ta = t0; ta < t1; ta += kSelThreads) {
+      const uint32_t t = ta + threadIdx.x;
+      int4 info = make_int4(0, 0, 0, 0);
+      if (t < t1) info = *reinterpret_cast<const int4*>(S.tl_info + (size_t)(base + t) * 4);
+      const uint32_t n = owned_by_lane(S, base + t, info);
+      const uint32_t s = info.w != 0 && (int)n >= K.n_min_track ? n : 0u;
+      mine += s != 0u ? 1u : 0u;
+      if (t == t0) first = s; else if (t < t1) S.tl_sel[t] = s;
     }
-    const int lo = wave_min(valid ? rin : kRows), hi = wave_max(valid ? rout : -1);
-    const TlList hits = tl_list(S, T);
-    int cnt = 0;
-    for (int r0 = lo; r0 <= hi; r0 += RB) {
-      int32_t hv[RB];
-      load_row_batch(S, hits, gr, r0, valid, rin, rout, hv);
-      uint32_t wv[RB];
-      load_weights(S, hv, wv);
-#pragma unroll
-      for (int u = 0; u < RB; ++u) cnt += (hv[u] >= 0 && wv[u] == w) ? 1 : 0;
-    }
-    if (t < total) S.tl_sel[t] = valid && cnt >= K.n_min_track ? 1u : 0u;
+    if (mine) atomicAdd(&selected, mine);
+    __syncthreads();
+    if (threadIdx.x == 0) S.tl_sel[t0] = first | selected << 8;
+    return;
   }
+  for (uint32_t ta = t0; ta < t1; ta += kSelRound) {
+    const uint32_t t = ta + threadIdx.x / kSelLanes;
+    const uint32_t T = base + t;
+    int4 info = make_int4(0, 0, 0, 0);
+    if (t < t1) info = *reinterpret_cast<const int4*>(S.tl_info + (size_t)T * 4);
+    uint32_t n = 0;
+    if (info.w != 0) {
+      int32_t hv[8];
+      n = (uint32_t)__popc(owned_rows(S, T, info, b, hv));
+    }
+#pragma unroll
+    for (int d = kSelLanes / 2; d > 0; d >>= 1) n += (uint32_t)__shfl_xor((int)n, d, 64);
+    if (b == 0 && t < t1) {
+      const uint32_t s = info.w != 0 && (int)n >= K.n_min_track ? n : 0u;
+      mine += s != 0u ? 1u : 0u;
+      if (t == t0) first = s; else S.tl_sel[t] = s;
+    }
+  }
+  if (b == 0 && mine) atomicAdd(&selected, mine);
+  __syncthreads();
+  if (threadIdx.x == 0) S.tl_sel[t0] = first | selected << 8;
 }
 
 // Selected tracklets -> tracks of the range (in tracklet order), each with
-// its owned hits compacted (ascending row).  Lane per tracklet, rows walked
-// together by the wave as in k_select.  The range's track region holds
-// every track its hits allow (each owns >= n_min_track hits of its own); a
-// position beyond it is not written and raises the capacity error.
-template <int RB>
-__global__ void __launch_bounds__(256) k_track_write(Slot S, int g0, int ns) {
+// its owned hits compacted (ascending row).  A block adds up the chunks
+// before its own, lists its chunk's selected tracklets 256 at a time and
+// writes them kSelRound together.  The range's track region holds every track
+// its hits allow (each owns >= n_min_track hits of its own); a position
+// beyond it is not written and raises the capacity error.
+__global__ void __launch_bounds__(kSelThreads) k_track_write(Slot S, int g0, int ns) {
+  __shared__ uint32_t list[kSelThreads];
+  __shared__ uint32_t wsum[kSelThreads / 64];
   const uint32_t total = S.range_cnt[0];
-  const uint32_t ntk = S.range_cnt[1];
   const uint32_t tl0 = S.tl_base[g0], tk0 = S.tk_base[g0];
   const uint32_t tk_room = S.tk_base[g0 + ns] - tk0;
-  const uint32_t lane = threadIdx.x & 63;
-  const XcdChunk xc = xcd_chunk(total);
-  for (uint32_t tb = xc.first; tb < xc.end; tb += xc.stride) {
-    const uint32_t t = tb + lane;
-    const uint32_t T = tl0 + t;
-    bool sel = false;
-    uint32_t k = 0, w = 0;
-    int rin = 1, rout = 0;
-    int gr = 0;
-    if (t < total) {
-      const uint32_t pos = S.tl_sel[t];
-      const uint32_t next = t + 1 < total ? S.tl_sel[t + 1] : ntk;
-      sel = next != pos;
-      if (sel && pos >= tk_room) {
-        atomicOr(&S.err[2], 1u);
-        sel = false;
-      }
-      if (sel) {
-        k = tk0 + pos;
-        const int32_t* info = S.tl_info + (size_t)T * 4;
-        rin = info[1];
-        rout = info[2];
-        w = S.tl_weight[T];
-        gr = S.start_sr[T] / kRows * kRows;
-      }
-    }
-    const int lo = wave_min(sel ? rin : kRows), hi = wave_max(sel ? rout : -1);
-    const TlList hits = tl_list(S, T);
-    int32_t* own = S.tk_own + (size_t)k * kRows;
-    uint8_t* own_row = S.tk_own_row + (size_t)k * kRows;
-    int cnt = 0;
-    for (int r0 = lo; r0 <= hi; r0 += RB) {
-      int32_t hv[RB];
-      load_row_batch(S, hits, gr, r0, sel, rin, rout, hv);
-      uint32_t wv[RB];
-      load_weights(S, hv, wv);
+  const SelChunk c = sel_chunk(total);
+  const uint32_t chunks = max(1u, (total + c.size - 1) / c.size);   // one of no tracklets if there is none
+  if (c.index >= chunks) return;
+  const bool last = c.index == chunks - 1;
+  const uint32_t t0 = c.index * c.size, t1 = min(total, t0 + c.size);
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  // position of the chunk's first track
+  uint32_t pos = 0;
+  {
+    uint32_t v = 0;
+    for (uint32_t i = threadIdx.x; i < c.index; i += kSelThreads) v += S.tl_sel[i * c.size] >> 8;
 #pragma unroll
-      for (int u = 0; u < RB; ++u) {
-        if (hv[u] >= 0 && wv[u] == w) {
-          own[cnt] = hv[u];
-          own_row[cnt] = (uint8_t)(r0 + u);
-          ++cnt;
+    for (int d = 32; d > 0; d >>= 1) v += (uint32_t)__shfl_xor((int)v, d, 64);
+    if (lane == 0) wsum[w] = v;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < (int)kSelThreads / 64; ++i) pos += wsum[i];
+  }
+  const uint32_t b = threadIdx.x % kSelLanes;
+  for (uint32_t ta = t0; ta < t1; ta += kSelThreads) {
+    const uint32_t t = ta + threadIdx.x;
+    const bool sel = t < t1 && (S.tl_sel[t] & 0xFFu) != 0u;
+    const unsigned long long m = __ballot(sel);
+    __syncthreads();                                  // wsum and list are free
+    if (lane == 0) wsum[w] = (uint32_t)__popcll(m);
+    __syncthreads();
+    uint32_t before = 0, n_sel = 0;
+#pragma unroll
+    for (int i = 0; i < (int)kSelThreads / 64; ++i) {
+      if (i < w) before += wsum[i];
+      n_sel += wsum[i];
+    }
+    if (sel) list[before + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = t;
+    __syncthreads();
+    for (uint32_t j0 = 0; j0 < n_sel; j0 += kSelRound) {
+      const uint32_t j = j0 + threadIdx.x / kSelLanes;
+      const bool act = j < n_sel && pos + j < tk_room;
+      if (j < n_sel && !act && b == 0) atomicOr(&S.err[2], 1u);
+      uint32_t own = 0, T = 0;
+      int32_t hv[8];
+      if (act) {
+        T = tl0 + list[j];
+        const int4 info = *reinterpret_cast<const int4*>(S.tl_info + (size_t)T * 4);
+        own = owned_rows(S, T, info, b, hv);
+      }
+      const uint32_t n = (uint32_t)__popc(own);
+      uint32_t end = n;
+#pragma unroll
+      for (int d = 1; d < (int)kSelLanes; d <<= 1) {
+        const uint32_t x = (uint32_t)__shfl_up((int)end, d, kSelLanes);
+        if ((int)b >= d) end += x;
+      }
+      if (act) {
+        const uint32_t k = tk0 + pos + j;
+        int32_t* o = S.tk_own + (size_t)k * kRows;
+        uint8_t* orow = S.tk_own_row + (size_t)k * kRows;
+        uint32_t at = end - n;
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (own >> u & 1u) {
+            o[at] = hv[u];
+            orow[at] = (uint8_t)(b * 8 + u);
+            ++at;
+          }
+        if (b == kSelLanes - 1) {
+          S.tk_tracklet[k] = (int32_t)T;
+          S.tk_nown[k] = (int32_t)end;
         }
       }
     }
-    if (sel) {
-      S.tk_tracklet[k] = (int32_t)T;
-      S.tk_nown[k] = cnt;
-    }
+    pos += n_sel;
   }
-}
-
-void launch_select(int rb, int blocks, hipStream_t st, const Slot& S, const DevConst& K, int g0) {
-  switch (rb) {
-    case 4: k_select<4><<<blocks, 256, 0, st>>>(S, K, g0); break;
-    case 16: k_select<16><<<blocks, 256, 0, st>>>(S, K, g0); break;
-    default: k_select<8><<<blocks, 256, 0, st>>>(S, K, g0); break;
-  }
-}
-
-void launch_track_write(int rb, int blocks, hipStream_t st, const Slot& S, int g0, int ns) {
-  switch (rb) {
-    case 4: k_track_write<4><<<blocks, 256, 0, st>>>(S, g0, ns); break;
-    case 16: k_track_write<16><<<blocks, 256, 0, st>>>(S, g0, ns); break;
-    default: k_track_write<8><<<blocks, 256, 0, st>>>(S, g0, ns); break;
-  }
+  if (last && threadIdx.x == 0) S.range_cnt[1] = pos;
 }
 
 // The inward walk of one pass over the owned hits own[jmin .. n-1]

@@ -113,7 +113,7 @@ struct Slot {
   int32_t* tl_info;         // [tl capacity][4]: n, row_in, row_out, valid
   uint32_t* tl_weight;      // [tl capacity]
   float* tl_state;          // [tl capacity][5] inner state (y, z, s, T, Q)
-  uint32_t* tl_sel;         // [tl capacity+1] selected flag, then track positions
+  uint32_t* tl_sel;         // [tl capacity+1] hits owned if selected, else 0 (and chunk counts)
   uint32_t* weight;         // [n] per sorted hit, 0 = unowned
   // tracks (per-sector regions)
   int32_t* tk_tracklet;     // [tk capacity]

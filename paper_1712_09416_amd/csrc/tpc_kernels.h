@@ -6,9 +6,8 @@
 
 namespace tpc {
 
-// launchers of the kernels instantiated for tuning knobs (results never
-// depend on the knobs): wb = window hits read per round trip (2, 4, 8),
-// rb = hit-list rows read per round trip (4, 8, 16)
+// launchers of the kernels instantiated for a tuning knob (results never
+// depend on it): wb = window hits read per round trip (2, 4, 8)
 void launch_neighbours(int wb, int blocks, hipStream_t st, const Slot& S, const DevConst& K, int g0,
                        int ns);
 // waves that few tracklets / tracks are spread over: measured best of 512,
@@ -19,8 +18,6 @@ constexpr uint32_t kTrackletWaves = 2048;
 constexpr uint32_t kRefitWaves = 1024;
 void launch_tracklets(int wb, int blocks, int threads, hipStream_t st, const Slot& S,
                       const DevConst& K, int g0);
-void launch_select(int rb, int blocks, hipStream_t st, const Slot& S, const DevConst& K, int g0);
-void launch_track_write(int rb, int blocks, hipStream_t st, const Slot& S, int g0, int ns);
 // stage + grid
 __global__ void k_count(Slot S);
 __global__ void k_grid_begin(Slot S);
@@ -32,6 +29,9 @@ __global__ void k_row_sort_large(Slot S, DevConst K);
 // cellular automaton
 __global__ void k_clean_rows(Slot S, int g0, int ns, int n_min_chain);
 __global__ void k_start_write(Slot S, int g0, int ns);
+// selection (the same grid for both, a multiple of 8 blocks)
+__global__ void k_select(Slot S, DevConst K, int g0);
+__global__ void k_track_write(Slot S, int g0, int ns);
 // Kalman filter
 __global__ void k_refit(Slot S, DevConst K, int g0, int ns);
 // output
