@@ -487,10 +487,8 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   const int64_t n_range = range_clusters(h, g0, ns);
   const int64_t tl_bound = std::min<int64_t>(s.cap_tl, n_range / ctx->p.n_min_chain + ns);
   const int tl_block = ctx->p.tl_block;
-  // a wave per 64 tracklets, and enough waves to spread a few over the chip
-  const int nb_lane = std::max(
-      std::max(8, grid_stride_blocks(tl_bound, tl_block, 16384 * 64 / tl_block) / 8 * 8),
-      std::min(grid_stride_blocks(tl_bound * 64, tl_block), (int)kTrackletWaves * 64 / tl_block));
+  const int nb_lane =
+      std::max(8, grid_stride_blocks(tl_bound, tl_block, 16384 * 64 / tl_block) / 8 * 8);
   // 32 lanes a tracklet; a multiple of 8 blocks: each XCD walks its chunk of
   // the tracklets
   const int nb_sel = (grid_stride_blocks(tl_bound * 32, 256, 2048) + 7) / 8 * 8;
@@ -506,7 +504,7 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
            s.range_cnt + 0, false);
   k_start_write<<<nb_rows, 256, 0, st>>>(s, g0, ns);
   if (marks) mark(ctx, 3);
-  launch_tracklets(ctx->p.win_batch, nb_lane, ctx->p.tl_block, st, s, ctx->k, g0);
+  launch_tracklets(ctx->p.win_batch, tl_bound, nb_lane, ctx->p.tl_block, st, s, ctx->k, g0);
   if (marks) mark(ctx, 4);
   k_select<<<nb_sel, 256, 0, st>>>(s, ctx->k, g0);
   k_track_write<<<nb_sel, 256, 0, st>>>(s, g0, ns);

@@ -290,6 +290,8 @@ __device__ __forceinline__ void wave_add_u64(unsigned long long* dst, unsigned l
 // `most` waves.
 struct LaneGroup {
   uint32_t per, index;      // items per wave; this lane's item in the wave
+  uint32_t size, lane;      // lanes of a group, this lane's place in its own
+  unsigned long long mask;  // the group's lanes in the wave
   bool first;               // first lane of its group
 };
 __device__ __forceinline__ LaneGroup lane_group(uint32_t total, uint32_t most) {
@@ -299,7 +301,10 @@ __device__ __forceinline__ LaneGroup lane_group(uint32_t total, uint32_t most) {
   LaneGroup g;
   g.per = 64u >> sh;
   g.index = lane >> sh;
-  g.first = (lane & ((1u << sh) - 1u)) == 0u;
+  g.size = 1u << sh;
+  g.lane = lane & (g.size - 1u);
+  g.mask = (g.size == 64u ? ~0ull : (1ull << g.size) - 1ull) << (lane - g.lane);
+  g.first = g.lane == 0u;
   return g;
 }
 

@@ -3,6 +3,8 @@
 // and the decisions of its current block of 8 rows live in registers, its
 // hit list in global memory (row-indexed, a block written when the lane
 // leaves it).
+#include <algorithm>
+
 #include "tpc_device.h"
 #include "tpc_kernels.h"
 
@@ -16,24 +18,35 @@ __device__ __forceinline__ bool inside(const DevConst& K, const Helix<float>& h,
          !(zsign * h.z > K.mz);
 }
 
-// Best hit of row sr for the predicted state: inside
-// |r_y| <= min(k sqrt(S_yy), w_max), |r_z| <= min(k sqrt(S_zz), w_max),
-// smallest chi2, ties to the smaller cluster ID.  -1 if none; the hit record
-// is returned in `out`.  WB: hit records read per round trip.
+// The search window around a predicted state: |r_y| <= min(k sqrt(S_yy),
+// w_max), |r_z| <= min(k sqrt(S_zz), w_max).
+struct Window {
+  float wy, wz;
+};
+__device__ __forceinline__ Window search_window(const DevConst& K, const Resid<float>& w) {
+  float ry = sqrt_mid(w.s00), rz = sqrt_mid(w.s11);
+  if (!(mid_range(fminf(w.s00, w.s11)) && mid_range(fmaxf(w.s00, w.s11)))) {
+    ry = sqrtf(w.s00);
+    rz = sqrtf(w.s11);
+  }
+  Window x;
+  x.wy = K.kwin * ry;
+  if (x.wy > K.wmax) x.wy = K.wmax;
+  x.wz = K.kwin * rz;
+  if (x.wz > K.wmax) x.wz = K.wmax;
+  return x;
+}
+
+// Best hit of row sr for the predicted state: inside the window, smallest
+// chi2, ties to the smaller cluster ID.  -1 if none; the hit record is
+// returned in `out`.  By one lane; WB: hit records read per round trip.
 template <int WB>
 __device__ __forceinline__ int32_t search_row(const Slot& S, const DevConst& K, const RowBins& rb,
                                               const Helix<float>& h, float vy, float vz,
                                               unsigned& examined, Hit& out) {
   const Resid<float> w = resid_weights(h, vy, vz);
-  float ry0 = sqrt_mid(w.s00), rz0 = sqrt_mid(w.s11);
-  if (!(mid_range(fminf(w.s00, w.s11)) && mid_range(fmaxf(w.s00, w.s11)))) {
-    ry0 = sqrtf(w.s00);
-    rz0 = sqrtf(w.s11);
-  }
-  float wy = K.kwin * ry0;
-  if (wy > K.wmax) wy = K.wmax;
-  float wz = K.kwin * rz0;
-  if (wz > K.wmax) wz = K.wmax;
+  const Window win = search_window(K, w);
+  const float wy = win.wy, wz = win.wz;
   const float yc = h.y, zc = h.z;
   int32_t best = -1;
   float bchi = 0.0f;
@@ -54,6 +67,85 @@ __device__ __forceinline__ int32_t search_row(const Slot& S, const DevConst& K, 
   return best;
 }
 
+// The same search by the lanes of a group, all with the same state: each lane
+// tests its own candidates.  A short row (at most two hits a lane) is tested
+// whole, the first hit of each lane (hx, valid if the row has it) read before
+// the transport, so that the search waits for no memory; a longer one by the
+// bins the window touches, a lane taking every (size / 4)-th hit of every
+// fourth z row.  In a lone wave every instruction takes 8 cycles and every
+// read some 200 to 800: a lane by itself needs some 250 instructions and two
+// reads after one another for a search.
+__device__ __forceinline__ bool short_row(const LaneGroup& lg, uint32_t n) { return n <= 2u * lg.size; }
+__device__ __forceinline__ int32_t search_group(const Slot& S, const DevConst& K, const LaneGroup& lg,
+                                                uint32_t first, uint32_t n, const RowBins& rb,
+                                                const Hit& hx, const Helix<float>& h, float vy, float vz,
+                                                unsigned& examined, Hit& out) {
+  const Resid<float> w = resid_weights(h, vy, vz);
+  const Window win = search_window(K, w);
+  bool have = false;
+  float bchi = 0.0f;
+  uint32_t bp = 0;
+  Hit bx = hx;
+  auto test = [&](uint32_t p, const Hit& x) {
+    const float ry = x.y - h.y, rz = x.z - h.z;
+    if (!(fabsf(ry) <= win.wy && fabsf(rz) <= win.wz)) return;
+    ++examined;
+    const float ch = chi2_of(w, ry, rz);
+    if (!have || ch < bchi || (ch == bchi && x.id < bx.id)) {
+      have = true;
+      bchi = ch;
+      bp = p;
+      bx = x;
+    }
+  };
+  if (short_row(lg, n)) {
+    if (lg.lane < n) test(first + lg.lane, hx);
+    if (lg.size + lg.lane < n) {
+      const uint32_t p = first + lg.size + lg.lane;
+      test(p, S.hit[p]);
+    }
+  } else {
+    const float eps = 1e-3f;
+    const int iy0 = bin_y(rb, h.y - win.wy - eps), iy1 = bin_y(rb, h.y + win.wy + eps);
+    const int iz0 = bin_z(rb, h.z - win.wz - eps), iz1 = bin_z(rb, h.z + win.wz + eps);
+    const uint32_t* bo = S.bin_off + rb.base;
+    for (int izb = iz0; izb <= iz1; izb += 4) {
+      const int iz = izb + (int)(lg.lane & 3u);
+      uint32_t lo = 0u, hi = 0u;
+      if (iz <= iz1) {
+        lo = bo[iz * rb.ny + iy0];
+        hi = bo[iz * rb.ny + iy1 + 1];
+      }
+      for (uint32_t p = lo + (lg.lane >> 2); p < hi; p += lg.size >> 2) test(p, S.hit[p]);
+    }
+  }
+  unsigned long long m = __ballot(have) & lg.mask;
+  if (m == 0ull) return -1;
+  if (__popcll(m) > 1) {
+    float c = bchi;
+    uint32_t id = bx.id;
+    bool any = have;
+    for (uint32_t d = lg.size >> 1; d > 0u; d >>= 1) {
+      const float co = __shfl_xor(c, (int)d, 64);
+      const uint32_t io = (uint32_t)__shfl_xor((int)id, (int)d, 64);
+      const bool ho = __shfl_xor((int)any, (int)d, 64) != 0;
+      if (ho && (!any || co < c || (co == c && io < id))) {
+        c = co;
+        id = io;
+        any = true;
+      }
+    }
+    const unsigned long long best = __ballot(have && bchi == c && bx.id == id) & lg.mask;
+    if (best != 0ull) m = best;      // (0: chi2 is not a number, any hit will be refused)
+  }
+  const int win_lane = __ffsll((long long)m) - 1;
+  out.y = __shfl(bx.y, win_lane, 64);
+  out.z = __shfl(bx.z, win_lane, 64);
+  out.id = 0u;
+  out.upc = -1;
+  return __shfl((int)bp, win_lane, 64);
+}
+
 __device__ __forceinline__ bool try_hit(const DevConst& K, Helix<float>& h, const Hit& x, float vy,
                                         float vz, unsigned& tries) {
   float ch;
@@ -70,14 +162,14 @@ __device__ __forceinline__ bool try_hit(const DevConst& K, Helix<float>& h, cons
 //  in    restart at the outermost hit with the prior covariance and the
 //        outward (s, T, Q); rows down to 0: re-confirm the outward hit, else
 //        search; same gap rule.  The inward hits form the tracklet.
-template <int WB>
-__global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
-  __shared__ RowRadii R;
-  load_radii(S, R);
+// kGroup: a group of lg.size >= 8 lanes a tracklet, else a lane each (or a few
+// lanes, doing the same).
+template <int WB, bool kGroup>
+__device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K, const RowRadii& R, int g0,
+                                               uint32_t total, const LaneGroup& lg) {
   // Tracklets are ordered by (sector, row): give each XCD (blocks are
   // dispatched round-robin over the 8 XCDs) one contiguous chunk, so the
   // hits a chunk's lanes read stay in that XCD's L2.
-  const uint32_t total = S.range_cnt[0];
   const uint32_t base = S.tl_base[g0];
   constexpr uint32_t kXcd = 8;
   const uint32_t xcd = blockIdx.x % kXcd, j = blockIdx.x / kXcd;
@@ -86,7 +178,6 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
   const uint32_t c0 = xcd * chunk;
   const uint32_t c1 = min(total, c0 + chunk);
   unsigned n_tl = 0, n_visits = 0, n_examined = 0, n_tries = 0, tl_hits = 0;
-  const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
   const uint32_t waves = blockDim.x >> 6;
   const uint32_t t0 = c0 + (j * waves + (threadIdx.x >> 6)) * lg.per + lg.index;
   for (uint32_t t = t0; t < c1; t += nbx * waves * lg.per) {
@@ -141,12 +232,32 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     float x_prev = x_r0;
     float x_ahead = x_r1;
     int r = r0 + 1;
+    // a group's first hits of the current row and the next one, a step ahead
+    uint32_t f_lo = 0, f_hi = 0;
+    if (kGroup) {
+      f_lo = S.row_off[gr + r0 + 1];
+      f_hi = S.row_off[gr + r0 + 2];
+    }
     for (; r < kRows; ++r) {
       const float xr = x_ahead;
       x_ahead = R.x[min(r + 1, kRows - 1)];
       // reads independent of the state, issued before the transport: the
-      // row's bin range and the hit the chain link points to
-      const RowBins rb = S.bins[gr + r];
+      // row's bin range (a group: its hits, if it is short) and the hit the
+      // chain link points to
+      RowBins rb;
+      Hit hx;
+      uint32_t first, nrow = 0;
+      if (kGroup) {
+        first = f_lo;
+        nrow = f_hi - f_lo;
+        f_lo = f_hi;
+        f_hi = S.row_off[gr + min(r + 2, kRows)];
+        if (!short_row(lg, nrow)) rb = S.bins[gr + r];
+        else if (lg.lane < nrow) hx = S.hit[first + lg.lane];
+      } else {
+        rb = S.bins[gr + r];
+        first = (uint32_t)rb.first;
+      }
       Hit xnext;
       if (chain && next >= 0) xnext = S.hit[next];
       if ((r & 7) == 0) {          // into the next block of rows
@@ -169,11 +280,13 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
         if (got < 0) chain = false;
       }
       if (got < 0) {
-        const int32_t bh = search_row<WB>(S, K, rb, st, vy, vz, examined, xg);
+        const int32_t bh =
+            kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xg)
+                   : search_row<WB>(S, K, rb, st, vy, vz, examined, xg);
         if (bh >= 0 && try_hit(K, st, xg, vy, vz, tries)) got = bh;
       }
       if (got >= 0) {
-        block_set(blk, r & 7, (uint32_t)got - (uint32_t)rb.first);
+        block_set(blk, r & 7, (uint32_t)got - first);
         next = xg.upc;
         p_out = got;
         miss = 0;
@@ -227,10 +340,28 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     // entry would make the compiler wait inside every step
     asm volatile("" : "+v"(x_ahead), "+v"(f_next));
     r = rout - 1;
+    if (kGroup) {
+      f_lo = S.row_off[gr + max(rout - 1, 0)];
+      f_hi = S.row_off[gr + rout];
+      f_next = S.row_off[gr + max(rout - 2, 0)];
+    }
     for (; r >= 0; --r) {
       const float xr = x_ahead;
       x_ahead = R.x[max(r - 1, 0)];
-      const RowBins rb = S.bins[gr + r];
+      RowBins rb;
+      Hit hx;
+      uint32_t first, nrow = 0;
+      if (kGroup) {
+        first = f_lo;
+        nrow = f_hi - f_lo;
+        f_hi = f_lo;
+        f_lo = f_next;
+        if (!short_row(lg, nrow)) rb = S.bins[gr + r];
+        else if (lg.lane < nrow) hx = S.hit[first + lg.lane];
+      } else {
+        rb = S.bins[gr + r];
+        first = (uint32_t)rb.first;
+      }
       const int32_t uh = uh_next;
       const Hit xu = xu_next;
       // row r-1: its outward entry (this block or the one below) and the
@@ -239,7 +370,8 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       if (r - 1 >= r0)
         uh_next = entry_hit(block_get((r & 7) == 0 ? blk_dn : blk, (r - 1) & 7), f_next);
       if (uh_next >= 0) xu_next = S.hit[uh_next];
-      if (r - 2 >= r0) f_next = (uint32_t)S.row_off[gr + r - 2];
+      if (kGroup) f_next = S.row_off[gr + max(r - 2, 0)];
+      else if (r - 2 >= r0) f_next = (uint32_t)S.row_off[gr + r - 2];
       if (!transport(st, xr - x_prev, K.b, K.smax, K.kk, K.m2)) break;
       x_prev = xr;
       if (!inside(K, st, xr, zsign)) break;
@@ -249,11 +381,13 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
       if (uh >= 0 && try_hit(K, st, xu, vy, vz, tries)) got = uh;
       if (got < 0) {
         Hit xs;
-        const int32_t bh = search_row<WB>(S, K, rb, st, vy, vz, examined, xs);
+        const int32_t bh =
+            kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xs)
+                   : search_row<WB>(S, K, rb, st, vy, vz, examined, xs);
         if (bh >= 0 && try_hit(K, st, xs, vy, vz, tries)) got = bh;
       }
       {
-        const uint32_t e = got >= 0 ? (uint32_t)got - (uint32_t)rb.first : (uint32_t)kNoEntry;
+        const uint32_t e = got >= 0 ? (uint32_t)got - first : (uint32_t)kNoEntry;
         if (block_get(blk, r & 7) != e) {
           block_set(blk, r & 7, e);
           dirty = true;
@@ -281,10 +415,11 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
     }
     if (dirty) hits.store_block(cb, blk);
     visits += (unsigned)(rout - max(r, 0));
+    if (kGroup) n_examined += examined;   // each lane counted its own
     if (!lg.first) continue;         // one lane of the tracklet's group writes
     n_tl += 1u;
     n_visits += visits;
-    n_examined += examined;
+    if (!kGroup) n_examined += examined;
     n_tries += tries;
     tl_hits += (unsigned)n;
     int32_t* info = S.tl_info + (size_t)T * 4;
@@ -333,8 +468,39 @@ __global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
   wave_add_u64(&S.stats[7], n_tries);
 }
 
-void launch_tracklets(int wb, int blocks, int threads, hipStream_t st, const Slot& S,
+// A lane group a tracklet (up to kGroupTracklets of them) and a lane a
+// tracklet are two kernels: together they would need 145 registers, and the
+// second one four waves to a SIMD (at most 128).  Each leaves the other's
+// counts alone.  Where the line lies: with the 16384 tracklets or fewer of
+// this rule a group has 8 lanes or more.  A 60-track event 443 us by the
+// second kernel and 397 by this one, 200 tracks in one sector 496 and 473,
+// 2000 tracks 761 and 764; groups of 4 lanes were slower (2000 tracks in
+// 1.31 instead of 1.30 ms whole), as every search costs some 40 instructions
+// to bring the lanes' results together.
+__global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g0) {
+  __shared__ RowRadii R;
+  const uint32_t total = S.range_cnt[0];
+  if (total > kGroupTracklets) return;
+  load_radii(S, R);
+  const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
+  make_tracklets<1, true>(S, K, R, g0, total, lg);
+}
+
+template <int WB>
+__global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
+  __shared__ RowRadii R;
+  const uint32_t total = S.range_cnt[0];
+  if (total <= kGroupTracklets) return;
+  load_radii(S, R);
+  const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
+  make_tracklets<WB, false>(S, K, R, g0, total, lg);
+}
+
+void launch_tracklets(int wb, int64_t bound, int blocks, int threads, hipStream_t st, const Slot& S,
                       const DevConst& K, int g0) {
+  const int few = (int)std::min<int64_t>(kTrackletWaves * 64 / threads, (bound * 64 + threads - 1) / threads);
+  k_tracklets_few<<<(few + 7) / 8 * 8, threads, 0, st>>>(S, K, g0);
+  if (bound <= (int64_t)kGroupTracklets) return;
   switch (wb) {
     case 2: k_tracklets<2><<<blocks, threads, 0, st>>>(S, K, g0); break;
     case 8: k_tracklets<8><<<blocks, threads, 0, st>>>(S, K, g0); break;
