@@ -181,6 +181,14 @@ __device__ __forceinline__ void block_set(uint4& v, int k, uint32_t e) {
   v.z = lo ? v.z : a;
   v.w = lo ? v.w : b;
 }
+// the block moved up by one entry, e (16 bits) the new last one: eight rows
+// pushed one after the other stand at their places
+__device__ __forceinline__ void block_push(uint4& v, uint32_t e) {
+  v.x = __builtin_amdgcn_alignbit(v.y, v.x, 16);
+  v.y = __builtin_amdgcn_alignbit(v.z, v.y, 16);
+  v.z = __builtin_amdgcn_alignbit(v.w, v.z, 16);
+  v.w = __builtin_amdgcn_alignbit(e, v.w, 16);
+}
 __device__ __forceinline__ uint4 block_empty() {
   return make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
 }
@@ -366,7 +374,10 @@ __device__ __forceinline__ bool mid_range(float x) {
 // double the squares of four floats stay far from them.
 __device__ __forceinline__ float rcp_det(float x) {
   float y = rcp_mid(x);
-  if (!mid_range(x)) y = 1.0f / x;
+  if (!mid_range(x)) {
+    asm volatile("");        // a branch, not both results and a choice
+    y = 1.0f / x;
+  }
   return y;
 }
 __device__ __forceinline__ double rcp_det(double x) { return rcp_mid(x); }
@@ -382,7 +393,8 @@ template <> __device__ __forceinline__ double fma_(double a, double b, double c)
 // linearly with x; y advances by dx times the tangent of the mid-angle
 // (N/D below); z advances by T times the arc, the arc being the chord
 // times asin(u)/u = 1 + u^2/6 + 3u^4/40 (u = half chord * curvature).
-// Returns false, leaving the state untouched, if |sin phi| would pass smax.
+// Returns false if |sin phi| would pass smax, leaving the state untouched, or
+// (kAlways, for callers that then discard it) of no use: without a branch.
 // kCov = false moves the parameters only (the same arithmetic for them),
 // for callers that discard the covariance.
 // The roots and the reciprocal are the short ones: smax is a float below 1,
@@ -390,13 +402,14 @@ template <> __device__ __forceinline__ double fma_(double a, double b, double c)
 // in [1, 2^27].  (s0 alone may be past smax, as an update without a gate
 // leaves it: |s0| > 1 gives NaN here as it does in a general root; |s0| = 1
 // makes iD, and with it every entry that iD enters, NaN either way.)
-template <class F, bool kCov = true>
+template <class F, bool kCov = true, bool kAlways = false>
 __device__ __forceinline__ bool transport(Helix<F>& h, F dx, F b, F smax, F kk = F(0),
                                           F m2 = F(0)) {
   const F one = F(1), half = F(0.5), two = F(2);
   const F bq = b * h.q;
   const F s1 = fma_(bq, dx, h.s);
-  if (!(fabs_(s1) <= smax)) return false;
+  const bool ok = fabs_(s1) <= smax;
+  if (!kAlways && !ok) return false;
   const F s0 = h.s;
   const F c0 = sqrt_mid(fma_(-s0, s0, one));
   const F c1 = sqrt_mid(fma_(-s1, s1, one));
@@ -431,7 +444,7 @@ __device__ __forceinline__ bool transport(Helix<F>& h, F dx, F b, F smax, F kk =
   h.y = fma_(dx, tmid, h.y);
   h.z = fma_(h.t, arc, h.z);
   h.s = s1;
-  if (!kCov) return true;
+  if (!kCov) return ok;
 
   F* c = h.c;
   const F yy = c[0], zy = c[1], zz = c[2], sy = c[3], sz = c[4], ss = c[5];
@@ -481,7 +494,7 @@ __device__ __forceinline__ bool transport(Helix<F>& h, F dx, F b, F smax, F kk =
     c[13] = fma_(th2, h.q * h.t * t2, c[13]);
     c[14] = fma_(th2, h.q * h.q * (h.t * h.t), c[14]);
   }
-  return true;
+  return ok;
 }
 
 // Inverse of the 2x2 residual covariance S = C_(y,z) + diag(vy, vz).
@@ -511,12 +524,18 @@ __device__ __forceinline__ F chi2_of(const Resid<F>& w, F ry, F rz) {
   return fma_(ry, fma_(w.w00, ry, w.w01 * rz), rz * fma_(w.w01, ry, w.w11 * rz));
 }
 
-// State and covariance after the measurement with residual (ry, rz), w the
-// residual weights of this state.  gated: refuse (state untouched) when a
-// variance would not stay positive or |sin phi| would reach smax.
+// Kalman update with the measurement (my, mz).  gated: refuse (state
+// untouched) when chi2 > chi2max, a variance would not stay positive or
+// |sin phi| would reach smax (one test of all of them: a branch of its own
+// for each costs a lone wave more than what it skips).
 template <class F>
-__device__ __forceinline__ bool kalman_apply(Helix<F>& h, const Resid<F>& w, F ry, F rz, F smax,
-                                             bool gated) {
+__device__ __forceinline__ bool kalman_update(Helix<F>& h, F my, F mz, F vy, F vz, F chi2max,
+                                              F smax, bool gated, F* chi2_out) {
+  const Resid<F> w = resid_weights(h, vy, vz);
+  const F ry = my - h.y;
+  const F rz = mz - h.z;
+  const F chi2 = chi2_of(w, ry, rz);
+  *chi2_out = chi2;
   const F* c = h.c;
   // covariance column of each state entry with y and with z
   const F cy[5] = {c[0], c[1], c[3], c[6], c[10]};
@@ -540,26 +559,12 @@ __device__ __forceinline__ bool kalman_apply(Helix<F>& h, const Resid<F>& w, F r
     for (int j = 0; j <= i; ++j, ++k) o.c[k] = fma_(-ky[i], cy[j], fma_(-kz[i], cz[j], c[k]));
   }
   if (gated) {
-    if (!(o.c[0] > F(0) && o.c[2] > F(0) && o.c[5] > F(0) && o.c[9] > F(0) && o.c[14] > F(0) &&
-          fabs_(o.s) < smax))
-      return false;
+    const bool ok = (chi2 <= chi2max) & (o.c[0] > F(0)) & (o.c[2] > F(0)) & (o.c[5] > F(0)) &
+                    (o.c[9] > F(0)) & (o.c[14] > F(0)) & (fabs_(o.s) < smax);
+    if (!ok) return false;
   }
   h = o;
   return true;
-}
-
-// Kalman update with the measurement (my, mz).  gated: also refused when
-// chi2 > chi2max.
-template <class F>
-__device__ __forceinline__ bool kalman_update(Helix<F>& h, F my, F mz, F vy, F vz, F chi2max,
-                                              F smax, bool gated, F* chi2_out) {
-  const Resid<F> w = resid_weights(h, vy, vz);
-  const F ry = my - h.y;
-  const F rz = mz - h.z;
-  const F chi2 = chi2_of(w, ry, rz);
-  *chi2_out = chi2;
-  if (gated && !(chi2 <= chi2max)) return false;
-  return kalman_apply(h, w, ry, rz, smax, gated);
 }
 
 // Prior covariance: measurement variances in y and z at the hit, wide

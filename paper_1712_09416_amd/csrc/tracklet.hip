@@ -14,8 +14,10 @@ namespace tpc {
 // sideways, left the drift volume, or crossed the membrane (zsign = -1 on
 // the A side, 1 on the C side).
 __device__ __forceinline__ bool inside(const DevConst& K, const Helix<float>& h, float xr, float zsign) {
-  return fabsf(h.y) <= xr * K.tanh_half + K.medge && fabsf(h.z) <= K.z_max + K.mz &&
-         !(zsign * h.z > K.mz);
+  const bool sector = fabsf(h.y) <= xr * K.tanh_half + K.medge;
+  const bool volume = fabsf(h.z) <= K.z_max + K.mz;
+  const bool side = !(zsign * h.z > K.mz);
+  return sector & volume & side;      // one branch for all of them
 }
 
 // The search window around a predicted state: |r_y| <= min(k sqrt(S_yy),
@@ -25,7 +27,8 @@ struct Window {
 };
 __device__ __forceinline__ Window search_window(const DevConst& K, const Resid<float>& w) {
   float ry = sqrt_mid(w.s00), rz = sqrt_mid(w.s11);
-  if (!(mid_range(fminf(w.s00, w.s11)) && mid_range(fmaxf(w.s00, w.s11)))) {
+  if (!mid_range(fminf(w.s00, w.s11)) || !mid_range(fmaxf(w.s00, w.s11))) {
+    asm volatile("");        // a branch, not both results and a choice
     ry = sqrtf(w.s00);
     rz = sqrtf(w.s11);
   }
@@ -38,8 +41,8 @@ __device__ __forceinline__ Window search_window(const DevConst& K, const Resid<f
 }
 
 // Best hit of row sr for the predicted state: inside the window, smallest
-// chi2, ties to the smaller cluster ID.  -1 if none; the hit record is
-// returned in `out`.  By one lane; WB: hit records read per round trip.
+// chi2, ties to the smaller cluster ID.  -1 if none; its place is
+// returned in `out` (y and z only).  By one lane; WB: hit records read per round trip.
 template <int WB>
 __device__ __forceinline__ int32_t search_row(const Slot& S, const DevConst& K, const RowBins& rb,
                                               const Helix<float>& h, float vy, float vz,
@@ -61,7 +64,8 @@ __device__ __forceinline__ int32_t search_row(const Slot& S, const DevConst& K, 
       best = (int32_t)p;
       bchi = ch;
       bid = id;
-      out = x;
+      out.y = x.y;
+      out.z = x.z;
     }
   });
   return best;
@@ -141,8 +145,6 @@ __device__ __forceinline__ int32_t search_group(const Slot& S, const DevConst& K
   const int win_lane = __ffsll((long long)m) - 1;
   out.y = __shfl(bx.y, win_lane, 64);
   out.z = __shfl(bx.z, win_lane, 64);
-  out.id = 0u;
-  out.upc = -1;
   return __shfl((int)bp, win_lane, 64);
 }
 
@@ -162,6 +164,13 @@ __device__ __forceinline__ bool try_hit(const DevConst& K, Helix<float>& h, cons
 //  in    restart at the outermost hit with the prior covariance and the
 //        outward (s, T, Q); rows down to 0: re-confirm the outward hit, else
 //        search; same gap rule.  The inward hits form the tracklet.
+// What bounds it is the count of instructions: a wave alone on its SIMD issues
+// one every 8 cycles, and some 320 steps follow one another; with four waves
+// to a SIMD the vector unit is busy.  So a step has one branch for all its stop
+// rules, transports without looking whether it may, and the hit list's block is
+// shifted in row by row (four instructions; placing an entry takes 15).
+// With these 60 tracks went from 397 to 362 us, 200 in one sector from 473 to
+// 436, 2000 from 761 to 703, 15000 from 1255 to 1180.
 // kGroup: a group of lg.size >= 8 lanes a tracklet, else a lane each (or a few
 // lanes, doing the same).
 template <int WB, bool kGroup>
@@ -213,10 +222,12 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
       const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
       reset_cov(st, sy * sy, sz * sz, K.cs0, K.ct0, K.cq0);
     }
-    // the hit list's block of the current row, in registers
+    // the hit list's block of the current row, in registers: the rows are
+    // pushed as they are left, up to row `pushed`
     int cb = r0 >> 3;
     uint4 blk = block_empty();
-    block_set(blk, r0 & 7, (uint32_t)p0 - first0);
+    block_push(blk, (uint32_t)p0 - first0);
+    int pushed = r0;
 
     // outward
     float l_y = st.y, l_z = st.z, l_s = st.s, l_t = st.t, l_q = st.q;   // at the last hit
@@ -231,14 +242,16 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
     // the seed has used, so no read before the loop is waited for inside it
     float x_prev = x_r0;
     float x_ahead = x_r1;
-    int r = r0 + 1;
+    int r = r0;
     // a group's first hits of the current row and the next one, a step ahead
     uint32_t f_lo = 0, f_hi = 0;
     if (kGroup) {
       f_lo = S.row_off[gr + r0 + 1];
       f_hi = S.row_off[gr + r0 + 2];
     }
-    for (; r < kRows; ++r) {
+    bool live = true;
+    do {
+      ++r;
       const float xr = x_ahead;
       x_ahead = R.x[min(r + 1, kRows - 1)];
       // reads independent of the state, issued before the transport: the
@@ -258,51 +271,53 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
         rb = S.bins[gr + r];
         first = (uint32_t)rb.first;
       }
-      Hit xnext;
-      if (chain && next >= 0) xnext = S.hit[next];
+      const bool direct = chain & (next >= 0);
+      Hit xg;
+      if (direct) xg = S.hit[next];
       if ((r & 7) == 0) {          // into the next block of rows
         hits.store_block(cb, blk);
         cb = r >> 3;
         blk = block_empty();
       }
-      if (!transport(st, xr - x_prev, K.b, K.smax, K.kk, K.m2)) break;
+      live = transport<float, true, true>(st, xr - x_prev, K.b, K.smax, K.kk, K.m2);
+      const bool in = inside(K, st, xr, zsign);
+      live = live & in;
       x_prev = xr;
-      if (!inside(K, st, xr, zsign)) break;
-      const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
-      const float vy = sy * sy, vz = sz * sz;
-      int32_t got = -1;
-      Hit xg;
-      if (chain) {
-        if (next >= 0) {
-          xg = xnext;
-          if (try_hit(K, st, xg, vy, vz, tries)) got = next;
+      if (live) {
+        const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
+        const float vy = sy * sy, vz = sz * sz;
+        int32_t hit = next;
+        bool got = false;
+        if (direct) got = try_hit(K, st, xg, vy, vz, tries);
+        if (!got) {
+          chain = false;
+          hit = kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xg)
+                       : search_row<WB>(S, K, rb, st, vy, vz, examined, xg);
+          if (hit >= 0) got = try_hit(K, st, xg, vy, vz, tries);
         }
-        if (got < 0) chain = false;
+        block_push(blk, got ? (uint32_t)hit - first : (uint32_t)kNoEntry);
+        pushed = r;
+        if (got) {
+          if (chain) next = xg.upc;
+          p_out = hit;
+          miss = 0;
+          l_y = st.y;
+          l_z = st.z;
+          l_s = st.s;
+          l_t = st.t;
+          l_q = st.q;
+          rout = r;
+          x_rout = xr;
+        } else {
+          live = ++miss < K.n_gap;
+        }
       }
-      if (got < 0) {
-        const int32_t bh =
-            kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xg)
-                   : search_row<WB>(S, K, rb, st, vy, vz, examined, xg);
-        if (bh >= 0 && try_hit(K, st, xg, vy, vz, tries)) got = bh;
-      }
-      if (got >= 0) {
-        block_set(blk, r & 7, (uint32_t)got - first);
-        next = xg.upc;
-        p_out = got;
-        miss = 0;
-        l_y = st.y;
-        l_z = st.z;
-        l_s = st.s;
-        l_t = st.t;
-        l_q = st.q;
-        rout = r;
-        x_rout = xr;
-      } else if (++miss >= K.n_gap) {
-        break;
-      }
-    }
+    } while (live && r < kRows - 1);
+    // the last block's entries to their places (unless it is still empty)
+    if ((pushed >> 3) == cb)
+      for (int k = pushed & 7; k < 7; ++k) block_push(blk, kNoEntry);
     hits.store_block(cb, blk);
-    visits += (unsigned)(min(r, kRows - 1) - r0);
+    visits += (unsigned)(r - r0);
 
     // inward, covariance reset at the outermost hit
     const Hit xo = S.hit[p_out];
@@ -322,13 +337,14 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
     miss = 0;
     // the blocks of the current row and of the one below, in registers (the
     // outward decisions, rewritten as the inward ones are taken; a block is
-    // stored back only if an entry changed); the outward hit of the next
-    // row down loaded one step ahead, the first hit of the row below it two
-    // steps ahead
-    cb = (rout - 1) >> 3;
-    blk = hits.load_block(cb);
-    uint4 blk_dn = cb > 0 ? hits.load_block(cb - 1) : block_empty();
-    bool dirty = false;
+    // stored back only if an entry changed or the outward phase has not
+    // written it); the outward hit of the next row down loaded one step
+    // ahead, the first hit of the row below it two steps ahead
+    const int cb0 = r0 >> 3;
+    cb = max(rout - 1, 0) >> 3;
+    bool dirty = cb < cb0;
+    blk = dirty ? block_empty() : hits.load_block(cb);
+    uint4 blk_dn = cb > cb0 ? hits.load_block(cb - 1) : block_empty();
     const uint32_t f_a = rout - 1 >= r0 ? (uint32_t)S.row_off[gr + rout - 1] : 0u;
     uint32_t f_next = rout - 2 >= r0 ? (uint32_t)S.row_off[gr + rout - 2] : 0u;
     int32_t uh_next = rout - 1 >= r0 ? entry_hit(block_get(blk, (rout - 1) & 7), f_a) : -1;
@@ -339,13 +355,15 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
     // wait for these reads here, once: a read still in flight at the loop's
     // entry would make the compiler wait inside every step
     asm volatile("" : "+v"(x_ahead), "+v"(f_next));
-    r = rout - 1;
+    r = rout;
     if (kGroup) {
       f_lo = S.row_off[gr + max(rout - 1, 0)];
       f_hi = S.row_off[gr + rout];
       f_next = S.row_off[gr + max(rout - 2, 0)];
     }
-    for (; r >= 0; --r) {
+    live = rout > 0;
+    while (live) {
+      --r;
       const float xr = x_ahead;
       x_ahead = R.x[max(r - 1, 0)];
       RowBins rb;
@@ -372,49 +390,51 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
       if (uh_next >= 0) xu_next = S.hit[uh_next];
       if (kGroup) f_next = S.row_off[gr + max(r - 2, 0)];
       else if (r - 2 >= r0) f_next = (uint32_t)S.row_off[gr + r - 2];
-      if (!transport(st, xr - x_prev, K.b, K.smax, K.kk, K.m2)) break;
+      live = transport<float, true, true>(st, xr - x_prev, K.b, K.smax, K.kk, K.m2);
+      const bool in = inside(K, st, xr, zsign);
+      live = live & in;
       x_prev = xr;
-      if (!inside(K, st, xr, zsign)) break;
-      const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
-      const float vy = sy * sy, vz = sz * sz;
-      int32_t got = -1;
-      if (uh >= 0 && try_hit(K, st, xu, vy, vz, tries)) got = uh;
-      if (got < 0) {
-        Hit xs;
-        const int32_t bh =
-            kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xs)
-                   : search_row<WB>(S, K, rb, st, vy, vz, examined, xs);
-        if (bh >= 0 && try_hit(K, st, xs, vy, vz, tries)) got = bh;
-      }
-      {
-        const uint32_t e = got >= 0 ? (uint32_t)got - first : (uint32_t)kNoEntry;
-        if (block_get(blk, r & 7) != e) {
-          block_set(blk, r & 7, e);
-          dirty = true;
+      if (live) {
+        const float sy = sigma_y(K, st.z), sz = sigma_z(K, st.z);
+        const float vy = sy * sy, vz = sz * sz;
+        int32_t hit = uh;
+        bool got = false;
+        if (uh >= 0) got = try_hit(K, st, xu, vy, vz, tries);
+        if (!got) {
+          Hit xs;
+          hit = kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xs)
+                       : search_row<WB>(S, K, rb, st, vy, vz, examined, xs);
+          if (hit >= 0) got = try_hit(K, st, xs, vy, vz, tries);
+          if (!got) hit = -1;
+          if (hit != uh) {            // not what the outward phase found
+            block_set(blk, r & 7, got ? (uint32_t)hit - first : (uint32_t)kNoEntry);
+            dirty = true;
+          }
         }
-      }
-      if (got >= 0) {
-        ++n;
-        miss = 0;
-        l_y = st.y;
-        l_z = st.z;
-        l_s = st.s;
-        l_t = st.t;
-        l_q = st.q;
-        rin = r;
-      } else if (++miss >= K.n_gap) {
-        break;
-      }
-      if ((r & 7) == 0 && r > 0) {   // into the block below
-        if (dirty) hits.store_block(cb, blk);
-        dirty = false;
-        --cb;
-        blk = blk_dn;
-        blk_dn = cb > 0 ? hits.load_block(cb - 1) : block_empty();
+        if (got) {
+          ++n;
+          miss = 0;
+          l_y = st.y;
+          l_z = st.z;
+          l_s = st.s;
+          l_t = st.t;
+          l_q = st.q;
+          rin = r;
+        } else {
+          live = ++miss < K.n_gap;
+        }
+        live = live & (r > 0);
+        if (live & ((r & 7) == 0)) {   // into the block below
+          if (dirty) hits.store_block(cb, blk);
+          --cb;
+          dirty = cb < cb0;
+          blk = blk_dn;
+          blk_dn = cb > cb0 ? hits.load_block(cb - 1) : block_empty();
+        }
       }
     }
     if (dirty) hits.store_block(cb, blk);
-    visits += (unsigned)(rout - max(r, 0));
+    visits += (unsigned)(rout - r);
     if (kGroup) n_examined += examined;   // each lane counted its own
     if (!lg.first) continue;         // one lane of the tracklet's group writes
     n_tl += 1u;
@@ -470,7 +490,8 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
 
 // A lane group a tracklet (up to kGroupTracklets of them) and a lane a
 // tracklet are two kernels: together they would need 145 registers, and the
-// second one four waves to a SIMD (at most 128).  Each leaves the other's
+// second one four waves to a SIMD (at most 128: kept there by the launch
+// bound, at 9 spilled words outside of the rows' loops; 8 hits a read need 152).  Each leaves the other's
 // counts alone.  Where the line lies: with the 16384 tracklets or fewer of
 // this rule a group has 8 lanes or more.  A 60-track event 443 us by the
 // second kernel and 397 by this one, 200 tracks in one sector 496 and 473,
@@ -487,7 +508,7 @@ __global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g
 }
 
 template <int WB>
-__global__ void __launch_bounds__(256) k_tracklets(Slot S, DevConst K, int g0) {
+__global__ void __launch_bounds__(256, WB == 8 ? 1 : 4) k_tracklets(Slot S, DevConst K, int g0) {
   __shared__ RowRadii R;
   const uint32_t total = S.range_cnt[0];
   if (total <= kGroupTracklets) return;
