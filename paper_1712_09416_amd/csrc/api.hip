@@ -40,11 +40,6 @@ struct SlotHost {
 };
 
 // __global__ helpers local to this file
-__global__ void k_zero_u32(uint32_t* p, int64_t n) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) p[i] = 0u;
-}
-
 __global__ void k_kf_step(DevConst K, float* state, const float* dx, const float* meas, float* result,
                           int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -189,9 +184,6 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   m.in_off = c.take<uint32_t>(SR + 1);
   m.in_cur = c.take<uint32_t>(SR);
   m.in_list = c.take<int32_t>(cap_tk);
-  m.out_off = c.take<uint32_t>(SR + 1);
-  m.out_cur = c.take<uint32_t>(SR);
-  m.out_list = c.take<int32_t>(cap_tk);
   m.op = c.take<double>(cap_tk * 5);
   m.oc = c.take<double>(cap_tk * 15);
   m.ok = c.take<int32_t>(cap_tk);
@@ -210,6 +202,8 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   m.pair_n = c.take<uint32_t>(kPairSegs * kPairPad);
   m.link_out = c.take<int32_t>(cap_tk);
   m.link_in = c.take<int32_t>(cap_tk);
+  m.heads = c.take<int32_t>(cap_tk);
+  m.head_n = c.take<uint32_t>(1);
   m.head_ok = c.take<int32_t>(cap_tk);
   m.nseg = c.take<int32_t>(cap_tk);
   m.nfit = c.take<int32_t>(cap_tk);
@@ -218,6 +212,7 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   m.chi2 = c.take<double>(cap_tk);
   m.emit = c.take<uint32_t>(cap_tk + 1);
   m.nh = c.take<uint32_t>(cap_tk + 1);
+  m.tile_sum = c.take<uint32_t>(2 * kOrderBlocks);
   m.into = c.take<int32_t>(cap_tk);
   m.tracks = c.take<tpc_track>(cap_tk);
   m.hits = c.take<int32_t>(N);
@@ -788,24 +783,15 @@ int tpc_merge(tpc_ctx* ctx, int slot, const tpc_merge_params* mp) {
   hipStream_t st = ctx->stream;
   const int64_t K = s.cap_tk;
   const int64_t ns = s.n_sectors;
-  // lane-per-track kernels in four-wave blocks: a block's waves go to the
-  // four SIMDs of one CU, so the working waves do not share SIMDs
-  const int nbt = grid_stride_blocks(K, 256, 2048);
+  // blocks of four waves: a block's waves go to the four SIMDs of one CU, so
+  // the working waves do not share SIMDs; a group of up to 64 lanes a track
+  // where tracks are few, a lane a track where there are many
+  const int nbt = std::max(grid_stride_blocks(K, 256, 2048), grid_stride_blocks(K * 64, 256, kRefitWaves / 4));
   const int nb = grid_stride_blocks(K, 256);
   const int64_t nsr = ns * kRows;
-  for (uint32_t* p : {m.in_off, m.out_off}) k_zero_u32<<<grid_stride_blocks(nsr + 1, 256), 256, 0, st>>>(p, nsr + 1);
-  for (uint32_t* p : {m.in_cur, m.out_cur}) k_zero_u32<<<grid_stride_blocks(nsr, 256), 256, 0, st>>>(p, nsr);
-  k_fill_i32<<<nb, 256, 0, st>>>(m.link_in, K, -1);
-  // per track: smallest chi2 as inner and as outer partner (bit pattern;
-  // all ones = none) and the partner reaching it
-  for (unsigned long long* p : {m.in_key, m.out_key})
-    k_fill_i32<<<grid_stride_blocks(2 * K, 256), 256, 0, st>>>(reinterpret_cast<int32_t*>(p),
-                                                               2 * K, -1);
-  for (int32_t* p : {m.best_in, m.best_out}) k_fill_i32<<<nb, 256, 0, st>>>(p, K, 0x7FFFFFFF);
-  k_zero_u32<<<grid_stride_blocks(kPairSegs * kPairPad, 256), 256, 0, st>>>(m.pair_n, kPairSegs * kPairPad);
+  k_mg_begin<<<grid_stride_blocks(std::max(nsr + 1, K), 256), 256, 0, st>>>(s, m);
   k_mg_count<<<nb, 256, 0, st>>>(s, m);
   scan_u32(st, m.in_off, nullptr, nsr, s.scan_b, nullptr);
-  scan_u32(st, m.out_off, nullptr, nsr, s.scan_b, nullptr);
   k_mg_scatter<<<nb, 256, 0, st>>>(s, m);
   k_mg_outer<<<nbt, 256, 0, st>>>(s, ctx->k, m, C);
   // one-wave blocks, four tracks each
@@ -815,14 +801,16 @@ int tpc_merge(tpc_ctx* ctx, int slot, const tpc_merge_params* mp) {
   // walks the candidates again only if the list overflowed (a smaller grid:
   // its blocks return at once otherwise)
   k_mg_pairs<true><<<std::min(nbp, 1024), 64, 0, st>>>(s, ctx->k, m, C);
-  k_mg_final<<<nb, 256, 0, st>>>(s, m);
   k_mg_link<<<nb, 256, 0, st>>>(s, m);
   k_mg_chain<<<nbt, 256, 0, st>>>(s, ctx->k, m, C);
-  k_mg_emit<<<nb, 256, 0, st>>>(s, m);
-  scan_u32(st, m.emit, s.out_count, K, s.scan_b, nullptr);
-  scan_u32(st, m.nh, s.out_count, K, s.scan_b, nullptr);
-  k_mg_event_off<<<(h.n_events + 1 + 255) / 256, 256, 0, st>>>(s, m);
-  k_mg_write<<<nbt, 256, 0, st>>>(s, ctx->k, m);
+  // stretches of whole tiles, at most kOrderBlocks of them
+  const int64_t tiles = std::max<int64_t>(1, (K + kOrderTile - 1) / kOrderTile);
+  const int64_t chunk = (tiles + kOrderBlocks - 1) / kOrderBlocks * kOrderTile;
+  const unsigned nbo = (unsigned)std::max<int64_t>(1, (K + chunk - 1) / chunk);
+  k_mg_emit<<<nbo, 256, 0, st>>>(s, m, chunk);
+  k_mg_pos<<<nbo, 256, 0, st>>>(s, m, chunk);
+  // 16 lanes a track
+  k_mg_write<<<grid_stride_blocks(K * 16, 256, 4096), 256, 0, st>>>(s, ctx->k, m);
   TPC_LAUNCHED();
   h.merged = true;
   return record_done(ctx, h);

@@ -200,14 +200,19 @@ __device__ __forceinline__ const int32_t* track_hits(const Slot& S, const tpc_tr
   return S.out_hits + S.ev_hit_off[t.event] + t.hit_off;
 }
 
-// M1
+// M1, a lane group a track.  Bound like the refit: some 150 steps after one
+// another, each of some 330 instructions that a lone wave issues one by one
+// (2000 tracks 153 us with a lane a track, 142 so; 15000 tracks 160 either way,
+// where every wave has 32 of them).
 __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot M, MergeConst C) {
   __shared__ RowRadii R;
   load_radii(S, R);
   const uint32_t ntk = S.out_count[0];
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
-    const tpc_track t = S.out_tracks[a];
+  const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+  const LaneGroup lg = lane_group(ntk, min(kRefitWaves, waves));
+  const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  for (uint32_t a = wave * lg.per + lg.index; a < ntk; a += waves * lg.per) {
+    const tpc_track& t = S.out_tracks[a];
     const int64_t ev0 = S.ev_off[t.event];
     const int32_t* h = track_hits(S, t);
     Helix<double> st;
@@ -225,13 +230,14 @@ __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot 
     // hit after it and the list entry after that (indices clamped to the
     // last hit).
     const int nlast = t.n_hits - 1;
+    const int row_in = t.row_in, row_out = t.row_out;
     int k = 1;
     int64_t gn = ev0 + h[min(k, nlast)];
     int rn = k <= nlast ? (int)S.row[gn] : -1;
     int32_t h_after = h[min(k + 1, nlast)];
-    double x_lo = xrow(R, t.row_in);
-    float x_next = R.x[min(t.row_in + 1, kRows - 1)];
-    for (int r = t.row_in + 1; r <= t.row_out; ++r) {
+    double x_lo = xrow(R, row_in);
+    float x_next = R.x[min(row_in + 1, kRows - 1)];
+    for (int r = row_in + 1; r <= row_out; ++r) {
       const double x_hi = (double)x_next;
       x_next = R.x[min(r + 1, kRows - 1)];
       const float hy = S.y[gn], hz = S.z[gn];
@@ -250,6 +256,7 @@ __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot 
       rn = k <= nlast ? r_after : -1;
       h_after = h_after2;
     }
+    if (!lg.first) continue;
     M.ok[a] = ok ? 1 : 0;
     double* op = M.op + (size_t)a * 5;
     op[0] = st.y;
@@ -262,9 +269,31 @@ __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot 
   }
 }
 
-// track positions grouped by (event, sector, first row) and by (event,
-// sector, last row); the order inside a group does not matter (ties are
-// broken by track position)
+// Everything the merger counts into or takes minima of, cleared in one launch
+// (ten fills before, each some 9 us apart on the host's side).
+__global__ void k_mg_begin(Slot S, MergeSlot M) {
+  const uint32_t ntk = S.out_count[0];
+  const int64_t nsr = (int64_t)S.n_sectors * kRows;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t t0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  for (int64_t i = t0; i <= nsr; i += stride) {
+    M.in_off[i] = 0u;
+    if (i < nsr) M.in_cur[i] = 0u;
+  }
+  // per track: smallest chi2 as inner and as outer partner (bit pattern; all
+  // ones = none) and the partner reaching it
+  for (int64_t i = t0; i < (int64_t)ntk; i += stride) {
+    M.in_key[i] = ~0ull;
+    M.out_key[i] = ~0ull;
+    M.best_in[i] = 0x7FFFFFFF;
+    M.best_out[i] = 0x7FFFFFFF;
+  }
+  for (int64_t i = t0; i < (int64_t)kPairSegs * kPairPad; i += stride) M.pair_n[i] = 0u;
+  if (t0 == 0) M.head_n[0] = 0u;
+}
+
+// track positions grouped by (event, sector, first row); the order inside a
+// group does not matter (ties are broken by track position)
 __global__ void k_mg_count(Slot S, MergeSlot M) {
   const uint32_t ntk = S.out_count[0];
   const uint32_t stride = gridDim.x * blockDim.x;
@@ -272,7 +301,6 @@ __global__ void k_mg_count(Slot S, MergeSlot M) {
     const tpc_track& t = S.out_tracks[a];
     const int g = t.event * kSectorsPerEvent + t.sector;
     atomicAdd(&M.in_off[g * kRows + t.row_in], 1u);
-    atomicAdd(&M.out_off[g * kRows + t.row_out], 1u);
   }
 }
 
@@ -282,9 +310,8 @@ __global__ void k_mg_scatter(Slot S, MergeSlot M) {
   for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
     const tpc_track& t = S.out_tracks[a];
     const int g = t.event * kSectorsPerEvent + t.sector;
-    const int gi = g * kRows + t.row_in, go = g * kRows + t.row_out;
+    const int gi = g * kRows + t.row_in;
     M.in_list[M.in_off[gi] + atomicAdd(&M.in_cur[gi], 1u)] = (int32_t)a;
-    M.out_list[M.out_off[go] + atomicAdd(&M.out_cur[go], 1u)] = (int32_t)a;
   }
 }
 
@@ -484,28 +511,40 @@ __global__ void k_mg_pair_best(MergeSlot M) {
   }
 }
 
-// a track without a compatible partner: -1 and chi2 0
-__global__ void k_mg_final(Slot S, MergeSlot M) {
-  const uint32_t ntk = S.out_count[0];
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
-    const unsigned long long ki = M.in_key[a], ko = M.out_key[a];
-    M.chi_in[a] = ki == ~0ull ? 0.0 : __longlong_as_double((long long)ki);
-    if (ki == ~0ull) M.best_in[a] = -1;
-    M.chi_out[a] = ko == ~0ull ? 0.0 : __longlong_as_double((long long)ko);
-    if (ko == ~0ull) M.best_out[a] = -1;
-  }
-}
-
-// M3: mutual best pairs (link_in filled with -1 before)
+// The partners as results (a track without one: -1 and chi2 0) and M3, the
+// mutual best pairs.  A track's links are found from both its sides, so they
+// need no second launch: a partner's entry read here is one that its own lane
+// leaves alone (it has a compatible partner, this track).  The heads of chains
+// are listed, so that the refit's lanes are dealt to them alone.
 __global__ void k_mg_link(Slot S, MergeSlot M) {
   const uint32_t ntk = S.out_count[0];
   const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
-    const int32_t b = M.best_out[a];
-    const bool linked = b >= 0 && M.best_in[b] == (int32_t)a;
-    M.link_out[a] = linked ? b : -1;
-    if (linked) M.link_in[b] = (int32_t)a;
+  const uint32_t lane = threadIdx.x & 63;
+  for (uint32_t a0 = blockIdx.x * blockDim.x + (threadIdx.x & ~63u); a0 < ntk; a0 += stride) {
+    const uint32_t a = a0 + lane;
+    bool head = false;
+    if (a < ntk) {
+      const unsigned long long ki = M.in_key[a], ko = M.out_key[a];
+      const int32_t p = ki == ~0ull ? -1 : M.best_in[a];
+      const int32_t b = ko == ~0ull ? -1 : M.best_out[a];
+      M.chi_in[a] = p < 0 ? 0.0 : __longlong_as_double((long long)ki);
+      M.chi_out[a] = b < 0 ? 0.0 : __longlong_as_double((long long)ko);
+      if (p < 0) M.best_in[a] = -1;
+      if (b < 0) M.best_out[a] = -1;
+      const bool in = p >= 0 && M.best_out[p] == (int32_t)a;
+      const bool out = b >= 0 && M.best_in[b] == (int32_t)a;
+      M.link_in[a] = in ? p : -1;
+      M.link_out[a] = out ? b : -1;
+      M.head_ok[a] = 0;
+      head = out && !in;
+    }
+    const unsigned long long m = __ballot(head);
+    if (m == 0ull) continue;
+    const int leader = __ffsll((long long)m) - 1;
+    uint32_t base = 0;
+    if ((int)lane == leader) base = atomicAdd(M.head_n, (uint32_t)__popcll(m));
+    base = __shfl(base, leader, 64);
+    if (head) M.heads[base + (uint32_t)__popcll(m & ((1ull << lane) - 1ull))] = (int32_t)a;
   }
 }
 
@@ -677,15 +716,19 @@ __device__ bool carry_out(const DevConst& K, const RowRadii& R, const MergeConst
   return true;
 }
 
-// M4: refit of each chain (lane per chain head)
+// M4: refit of each chain, a lane group a chain.  Bound by the instructions
+// of some 3 x 150 steps after one another.  A lane per track, those that are
+// no heads idle, left 1 to 10 lanes of a wave at work, which then issues at
+// half the rate: 2000 tracks 692 us, now 526; 15000 tracks 702, now 632.
 __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot M, MergeConst C) {
   __shared__ RowRadii R;
   load_radii(S, R);
-  const uint32_t ntk = S.out_count[0];
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
-    M.head_ok[a] = 0;
-    if (M.link_in[a] >= 0 || M.link_out[a] < 0) continue;     // not the head of a chain
+  const uint32_t total = M.head_n[0];
+  const uint32_t waves = gridDim.x * (blockDim.x >> 6);
+  const LaneGroup lg = lane_group(total, min(kRefitWaves, waves));
+  const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  for (uint32_t i = wave * lg.per + lg.index; i < total; i += waves * lg.per) {
+    const uint32_t a = (uint32_t)M.heads[i];
     Chain ch;
     ch.n = 0;
     bool fits = true;
@@ -715,7 +758,7 @@ __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot 
       if (pass > 0) good = carry_out(K, R, C, ch, res, s0, t0, q0);
       if (good) good = chain_pass(S, K, R, C, ch, s0, t0, q0, res, chi2, nh);
     }
-    if (!good) continue;
+    if (!good || !lg.first) continue;
     M.head_ok[a] = 1;
     M.nseg[a] = ch.n;
     M.nfit[a] = nh;
@@ -737,12 +780,16 @@ __device__ __forceinline__ int32_t chain_head(const MergeSlot& M, int32_t a) {
   return h;
 }
 
-// output items: a refitted chain replaces its segments (at its head's
-// position), every other track stays
-__global__ void k_mg_emit(Slot S, MergeSlot M) {
-  const uint32_t ntk = S.out_count[0];
-  const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
+// Output items: a refitted chain replaces its segments (at its head's
+// position), every other track stays.  Blocks take a stretch of `chunk` tracks
+// each (a multiple of kOrderTile).  First each track's items and hits, with
+// the sums of every stretch:
+__global__ void __launch_bounds__(256) k_mg_emit(Slot S, MergeSlot M, int64_t chunk) {
+  const int64_t ntk = S.out_count[0];
+  const int64_t c0 = (int64_t)blockIdx.x * chunk;
+  const int64_t c1 = min(ntk, c0 + chunk);
+  uint32_t nt = 0, nh = 0;
+  for (int64_t a = c0 + threadIdx.x; a < c1; a += 256) {
     const int32_t h = chain_head(M, (int32_t)a);
     uint32_t e = 1, n = (uint32_t)S.out_tracks[a].n_hits;
     if (M.head_ok[h]) {
@@ -751,67 +798,142 @@ __global__ void k_mg_emit(Slot S, MergeSlot M) {
     }
     M.emit[a] = e;
     M.nh[a] = n;
+    nt += e;
+    nh += n;
+  }
+  uint32_t ex;
+  const uint32_t tt = block_scan256(nt, &ex), th = block_scan256(nh, &ex);
+  if (threadIdx.x == 0) {
+    M.tile_sum[2 * blockIdx.x] = tt;
+    M.tile_sum[2 * blockIdx.x + 1] = th;
   }
 }
 
-__global__ void k_mg_event_off(Slot S, MergeSlot M) {
-  const int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e > S.n_events) return;
-  const uint32_t k = S.ev_track_off[e];
-  M.ev_track_off[e] = M.emit[k];
-  M.ev_hit_off[e] = M.nh[k];
-}
-
-// n hit IDs from src to dst, eight loads in flight before their stores
-__device__ __forceinline__ void copy_hits(int32_t* dst, const int32_t* src, int n) {
-  for (int i0 = 0; i0 < n; i0 += 8) {
-    int32_t v[8];
+// Then each track's position and first hit, in place: a block adds up the
+// stretches before its own and scans its stretch tile by tile (two scans of
+// three launches each before).
+__global__ void __launch_bounds__(256) k_mg_pos(Slot S, MergeSlot M, int64_t chunk) {
+  const int64_t ntk = S.out_count[0];
+  const int64_t c0 = (int64_t)blockIdx.x * chunk;
+  const int64_t c1 = min(ntk, c0 + chunk);
+  if (c0 > 0 && c0 >= ntk) return;
+  uint32_t bt, bh;
+  {
+    uint32_t nt = 0, nh = 0, ex;
+    for (uint32_t i = threadIdx.x; i < blockIdx.x; i += 256) {
+      nt += M.tile_sum[2 * i];
+      nh += M.tile_sum[2 * i + 1];
+    }
+    bt = block_scan256(nt, &ex);
+    bh = block_scan256(nh, &ex);
+  }
+  for (int64_t i0 = c0; i0 < c1; i0 += kOrderTile) {
+    const int64_t i = i0 + (int64_t)threadIdx.x * 4;
+    uint32_t e[4], n[4], st = 0, sh = 0;
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = i0 + u < n ? src[i0 + u] : 0;
+    for (int u = 0; u < 4; ++u) {
+      e[u] = i + u < c1 ? M.emit[i + u] : 0u;
+      n[u] = i + u < c1 ? M.nh[i + u] : 0u;
+      st += e[u];
+      sh += n[u];
+    }
+    uint32_t et, eh;
+    const uint32_t tt = block_scan256(st, &et), th = block_scan256(sh, &eh);
+    et += bt;
+    eh += bh;
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (i0 + u < n) dst[i0 + u] = v[u];
+    for (int u = 0; u < 4; ++u) {
+      if (i + u < c1) {
+        M.emit[i + u] = et;
+        M.nh[i + u] = eh;
+      }
+      et += e[u];
+      eh += n[u];
+    }
+    bt += tt;
+    bh += th;
+  }
+  if (c1 == ntk && threadIdx.x == 0) {     // the stretch that ends the tracks
+    M.emit[ntk] = bt;
+    M.nh[ntk] = bh;
   }
 }
 
+constexpr uint32_t kWriteLanes = 16;   // lanes writing a track and its hits
+
+// n hit IDs from src to dst by the lanes of a group, four loads in flight
+// before their stores
+__device__ __forceinline__ void copy_hits(int32_t* dst, const int32_t* src, int n, int gl) {
+  for (int i0 = gl; i0 < n; i0 += 4 * (int)kWriteLanes) {
+    int32_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * (int)kWriteLanes;
+      v[u] = i < n ? src[i] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + u * (int)kWriteLanes;
+      if (i < n) dst[i] = v[u];
+    }
+  }
+}
+
+// Merged tracks and their hits, kWriteLanes lanes a track (a lane by itself
+// touches a line of its own with every word: 2000 tracks 45 us, now 24; 15000
+// tracks 55, now 43), and the per-event ranges.
 __global__ void __launch_bounds__(256) k_mg_write(Slot S, DevConst K, MergeSlot M) {
   const uint32_t ntk = S.out_count[0];
+  const uint32_t first = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t stride = gridDim.x * blockDim.x;
-  for (uint32_t a = blockIdx.x * blockDim.x + threadIdx.x; a < ntk; a += stride) {
+  for (uint32_t e = first; e <= (uint32_t)S.n_events; e += stride) {
+    const uint32_t k = S.ev_track_off[e];
+    M.ev_track_off[e] = M.emit[k];
+    M.ev_hit_off[e] = M.nh[k];
+  }
+  const int gl = (int)(threadIdx.x % kWriteLanes);
+  constexpr int kWords = (int)(sizeof(tpc_track) / 4), kHitOff = (int)(offsetof(tpc_track, hit_off) / 4);
+  for (uint32_t a = first / kWriteLanes; a < ntk; a += stride / kWriteLanes) {
     const int32_t h = chain_head(M, (int32_t)a);
     const bool merged = M.head_ok[h] != 0;
     const int32_t src = merged ? h : (int32_t)a;
-    M.into[a] = (int32_t)M.emit[src];
+    if (gl == 0) M.into[a] = (int32_t)M.emit[src];
     if (merged && h != (int32_t)a) continue;
     const uint32_t pos = M.emit[a];
     const uint32_t hpos = M.nh[a];
-    tpc_track o = S.out_tracks[a];
-    const int e = o.event;
+    const tpc_track& t = S.out_tracks[a];
     int32_t* dst = M.hits + hpos;
+    const int64_t hit_off = (int64_t)(hpos - M.nh[S.ev_track_off[t.event]]);
+    int last = h, nseg = 1;
     if (merged) {
-      int32_t last = h;
       int nh = 0;
       for (int32_t p = h; p >= 0; p = M.link_out[p]) {
-        const tpc_track T = S.out_tracks[p];
-        const int32_t* src_h = track_hits(S, T);
-        copy_hits(dst + nh, src_h, T.n_hits);
+        const tpc_track& T = S.out_tracks[p];
+        copy_hits(dst + nh, track_hits(S, T), T.n_hits, gl);
         nh += T.n_hits;
         last = p;
       }
-      o.n_hits = M.nfit[h];
-      o.row_out = S.out_tracks[last].row_out;
-      o.ndf = 2 * o.n_hits - 5;
-      for (int i = 0; i < 5; ++i) o.par[i] = M.par[(size_t)h * 5 + i];
-      for (int i = 0; i < 15; ++i) o.cov[i] = M.cov[(size_t)h * 15 + i];
-      o.chi2 = M.chi2[h];
-      M.out_nseg[pos] = M.nseg[h];
+      nseg = M.nseg[h];
+      if (gl == 0) {
+        tpc_track o = t;
+        o.n_hits = M.nfit[h];
+        o.row_out = S.out_tracks[last].row_out;
+        o.ndf = 2 * o.n_hits - 5;
+        for (int i = 0; i < 5; ++i) o.par[i] = M.par[(size_t)h * 5 + i];
+        for (int i = 0; i < 15; ++i) o.cov[i] = M.cov[(size_t)h * 15 + i];
+        o.chi2 = M.chi2[h];
+        o.hit_off = hit_off;
+        M.tracks[pos] = o;
+      }
     } else {
-      const int32_t* src_h = track_hits(S, o);
-      copy_hits(dst, src_h, o.n_hits);
-      M.out_nseg[pos] = 1;
+      copy_hits(dst, track_hits(S, t), t.n_hits, gl);
+      const uint32_t* from = reinterpret_cast<const uint32_t*>(&t);
+      uint32_t* to = reinterpret_cast<uint32_t*>(M.tracks + pos);
+      for (int w = gl; w < kWords; w += (int)kWriteLanes)
+        if (w != kHitOff && w != kHitOff + 1) to[w] = from[w];
+      if (gl == 0) M.tracks[pos].hit_off = hit_off;
     }
-    o.hit_off = (int64_t)(hpos - M.ev_hit_off[e]);
-    M.tracks[pos] = o;
+    if (gl == 0) M.out_nseg[pos] = nseg;
   }
 }
 

@@ -287,6 +287,34 @@ __device__ __forceinline__ void wave_add_u64(unsigned long long* dst, unsigned l
   if ((threadIdx.x & 63) == 0 && v) atomicAdd(dst, v);
 }
 
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int d = 1; d < 64; d <<= 1) {
+    const uint32_t t = __shfl_up(x, d, 64);
+    if (lane >= d) x += t;
+  }
+  return x;
+}
+
+// exclusive scan of one 256-thread block's values; returns the block total
+__device__ __forceinline__ uint32_t block_scan256(uint32_t v, uint32_t* excl) {
+  __shared__ uint32_t ws[4];
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  const uint32_t inc = wave_incl_scan(v);
+  if (lane == 63) ws[w] = inc;
+  __syncthreads();
+  uint32_t before = 0, tot = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (i < w) before += ws[i];
+    tot += ws[i];
+  }
+  __syncthreads();
+  *excl = before + inc - v;
+  return tot;
+}
+
 // How a wave's lanes are dealt to `total` items (tracklets, tracks): a lane
 // an item where there are many, a group of lanes an item where there are few,
 // so that these spread over the idle SIMDs: a wave's step costs what its

@@ -54,17 +54,17 @@ __global__ void k_out_count(Slot S, int64_t chunk);
 __global__ void k_out_order(Slot S, int64_t chunk);
 __global__ void k_write_out(Slot S);
 // cross-sector merger
+__global__ void k_mg_begin(Slot S, MergeSlot M);
 __global__ void k_mg_count(Slot S, MergeSlot M);
 __global__ void k_mg_scatter(Slot S, MergeSlot M);
 __global__ void k_mg_outer(Slot S, DevConst K, MergeSlot M, MergeConst C);
 template <bool kFinal>
 __global__ void k_mg_pairs(Slot S, DevConst K, MergeSlot M, MergeConst C);
-__global__ void k_mg_final(Slot S, MergeSlot M);
 __global__ void k_mg_pair_best(MergeSlot M);
 __global__ void k_mg_link(Slot S, MergeSlot M);
 __global__ void k_mg_chain(Slot S, DevConst K, MergeSlot M, MergeConst C);
-__global__ void k_mg_emit(Slot S, MergeSlot M);
-__global__ void k_mg_event_off(Slot S, MergeSlot M);
+__global__ void k_mg_emit(Slot S, MergeSlot M, int64_t chunk);
+__global__ void k_mg_pos(Slot S, MergeSlot M, int64_t chunk);
 __global__ void k_mg_write(Slot S, DevConst K, MergeSlot M);
 // drift-velocity calibration
 __global__ void k_cal_accumulate(Slot S, DevConst K, uint32_t* hist, int n_bins, double z_lo,

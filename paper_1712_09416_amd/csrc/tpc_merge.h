@@ -19,9 +19,6 @@ struct MergeSlot {
   uint32_t* in_off;         // [S*159+1] tracks per (event, sector, first row), then offsets
   uint32_t* in_cur;         // [S*159] scatter cursors
   int32_t* in_list;         // [K] track positions grouped by (event, sector, first row)
-  uint32_t* out_off;        // [S*159+1] the same by last row
-  uint32_t* out_cur;        // [S*159]
-  int32_t* out_list;        // [K]
   double* op;               // [K][5] state at the outermost hit
   double* oc;               // [K][15]
   int32_t* ok;              // [K] outer state exists
@@ -39,7 +36,9 @@ struct MergeSlot {
                             //     not all listed)
   uint32_t pair_cap;        // entries per segment
   int32_t* link_out;        // [K] mutual best outer partner, -1 none
-  int32_t* link_in;         // [K]
+  int32_t* link_in;         // [K] the same for the inner one
+  int32_t* heads;           // [K] heads of the chains of >= 2 segments, in no order
+  uint32_t* head_n;         // [1]
   int32_t* head_ok;         // [K] per chain head: chain of >= 2 segments refitted
   int32_t* nseg;            // [K] per chain head: segments
   int32_t* nfit;            // [K] per chain head: hits of the refitted chain
@@ -48,6 +47,7 @@ struct MergeSlot {
   double* chi2;             // [K]
   uint32_t* emit;           // [K+1] 1 per output track, then its output position
   uint32_t* nh;             // [K+1] its hit count, then its first hit
+  uint32_t* tile_sum;       // [kOrderBlocks][2] tracks and hits of a block's stretch
   int32_t* into;            // [K] output track of each input track
   tpc_track* tracks;        // [K] merged output, canonical order
   int32_t* hits;            // [n]
