@@ -40,6 +40,30 @@ struct SlotHost {
 };
 
 // __global__ helpers local to this file
+// Event offsets of a slot that come as a kernel argument: up to 128 events (1
+// KB of arguments), of which each launch has room for 4.  A copy from the
+// host's vector is staged by the runtime, some 10 us of the caller's time.
+constexpr int kArgEvents = 128;
+struct EventOffs {
+  int64_t v[kArgEvents + 1];
+};
+__global__ void k_event_off(int64_t* ev_off, EventOffs o, int n_events) {
+  for (int e = threadIdx.x; e <= n_events; e += blockDim.x) ev_off[e] = o.v[e];
+}
+
+// What a read-back needs first, into pinned host memory: the error words (if
+// given) and n entries of the per-event track and hit offsets.  One launch and
+// one wait; as copies into pageable memory these three cost the caller some 30
+// us each, one after the other.
+__global__ void k_read_head(const uint32_t* err, const uint32_t* track_off, const uint32_t* hit_off, int n,
+                            uint32_t* host) {
+  if (err && threadIdx.x < 4) host[threadIdx.x] = err[threadIdx.x];
+  for (int i = threadIdx.x; i < n; i += blockDim.x) {
+    host[4 + i] = track_off[i];
+    host[4 + n + i] = hit_off[i];
+  }
+}
+
 __global__ void k_kf_step(DevConst K, float* state, const float* dx, const float* meas, float* result,
                           int64_t n) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -345,6 +369,7 @@ thread_local std::string g_init_error;
 }  // namespace
 
 struct tpc_ctx {
+  uint32_t* head = nullptr;           // pinned: errors and offsets of a read-back
   DevConst k;
   RowTable x;
   tpc_params p;
@@ -395,6 +420,20 @@ void mark(tpc_ctx* ctx, int i) {
 int record_done(tpc_ctx* ctx, SlotHost& h) {
   if (!h.done) TPC_HIP(hipEventCreateWithFlags(&h.done, hipEventDisableTiming));
   TPC_HIP(hipEventRecord(h.done, ctx->stream));
+  return TPC_OK;
+}
+
+// k_read_head's words of n offsets each, read: host[0, 4) the errors, then the
+// track offsets, then the hit offsets
+int read_head(tpc_ctx* ctx, const uint32_t* err, const uint32_t* track_off, const uint32_t* hit_off, int n,
+              const uint32_t** host) {
+  if (!ctx->head)
+    TPC_HIP(hipHostMalloc(reinterpret_cast<void**>(&ctx->head),
+                          (4 + 2 * ((size_t)ctx->p.max_events + 1)) * sizeof(uint32_t), hipHostMallocDefault));
+  k_read_head<<<1, 256, 0, ctx->stream>>>(err, track_off, hit_off, n, ctx->head);
+  TPC_LAUNCHED();
+  TPC_HIP(hipStreamSynchronize(ctx->stream));
+  *host = ctx->head;
   return TPC_OK;
 }
 
@@ -576,8 +615,15 @@ int stage(tpc_ctx* ctx, int slot, int n_events, const int64_t* offs, const uint8
     s.y = h.own_y;
     s.z = h.own_z;
   }
-  TPC_HIP(hipMemcpyAsync(s.ev_off, h.ev_off.data(), (n_events + 1) * sizeof(int64_t),
-                         hipMemcpyHostToDevice, st));
+  if (n_events <= kArgEvents) {
+    EventOffs o;
+    std::copy(offs, offs + n_events + 1, o.v);
+    k_event_off<<<1, 256, 0, st>>>(s.ev_off, o, n_events);
+    TPC_LAUNCHED();
+  } else {
+    TPC_HIP(hipMemcpyAsync(s.ev_off, h.ev_off.data(), (n_events + 1) * sizeof(int64_t),
+                           hipMemcpyHostToDevice, st));
+  }
   h.state = 1;
   return record_done(ctx, h);
 }
@@ -828,19 +874,20 @@ int tpc_get_merged(tpc_ctx* ctx, int slot, int event, tpc_track* out, int64_t ma
     return ctx->fail(TPC_EINVAL, "null output buffer");
   if (!h.merged || h.state != 4) return ctx->fail(TPC_ESTATE, "slot not merged");
   hipStream_t st = ctx->stream;
-  uint32_t toff[2], hoff[2];
-  TPC_HIP(hipMemcpyAsync(toff, h.m.ev_track_off + event, sizeof(toff), hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipMemcpyAsync(hoff, h.m.ev_hit_off + event, sizeof(hoff), hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipStreamSynchronize(st));
+  const uint32_t* head;
+  const int rc = read_head(ctx, nullptr, h.m.ev_track_off + event, h.m.ev_hit_off + event, 2, &head);
+  if (rc) return rc;
+  const uint32_t *toff = head + 4, *hoff = head + 6;
   const int64_t nt = (int64_t)toff[1] - toff[0];
   const int64_t nh = (int64_t)hoff[1] - hoff[0];
   if (n_tracks) *n_tracks = nt;
   if (n_hits) *n_hits = nh;
   if (nt > max_tracks || nh > max_hits) return ctx->fail(TPC_EOVERFLOW, "output buffers too small");
   if (nt) TPC_HIP(hipMemcpyAsync(out, h.m.tracks + toff[0], nt * sizeof(tpc_track), hipMemcpyDeviceToHost, st));
+  if (nh) TPC_HIP(hipMemcpyAsync(hit_ids, h.m.hits + hoff[0], nh * 4, hipMemcpyDeviceToHost, st));
+  // last: into memory that is not pinned a copy holds the caller until it is done
   if (nt && n_segments)
     TPC_HIP(hipMemcpyAsync(n_segments, h.m.out_nseg + toff[0], nt * 4, hipMemcpyDeviceToHost, st));
-  if (nh) TPC_HIP(hipMemcpyAsync(hit_ids, h.m.hits + hoff[0], nh * 4, hipMemcpyDeviceToHost, st));
   TPC_HIP(hipStreamSynchronize(st));
   return TPC_OK;
 }
@@ -1140,11 +1187,10 @@ int tpc_get_tracks(tpc_ctx* ctx, int slot, int event, tpc_track* out, int64_t ma
   }
   if (h.state != 4) return ctx->fail(TPC_ESTATE, "slot not tracked");
   hipStream_t st = ctx->stream;
-  uint32_t err[4], toff[2], hoff[2];
-  TPC_HIP(hipMemcpyAsync(err, h.d.err, sizeof(err), hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipMemcpyAsync(toff, h.d.ev_track_off + event, sizeof(toff), hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipMemcpyAsync(hoff, h.d.ev_hit_off + event, sizeof(hoff), hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipStreamSynchronize(st));
+  const uint32_t* err;
+  const int rc = read_head(ctx, h.d.err, h.d.ev_track_off + event, h.d.ev_hit_off + event, 2, &err);
+  if (rc) return rc;
+  const uint32_t *toff = err + 4, *hoff = err + 6;
   if (err[0]) return ctx->fail(TPC_EINVAL, std::to_string(err[0]) + " invalid clusters (sector, row or coordinates)");
   if (err[1]) return ctx->fail(TPC_EINVAL, "a pad row holds more than 4096 clusters");
   if (err[2]) return ctx->fail(TPC_EDEVICE, "internal capacity exceeded");
@@ -1176,13 +1222,13 @@ int tpc_get_slot_tracks(tpc_ctx* ctx, int slot, tpc_track* out, int64_t max_trac
   if (h.state != 4) return ctx->fail(TPC_ESTATE, "slot not tracked");
   const int ne = std::max(1, h.n_events);
   hipStream_t st = ctx->stream;
-  uint32_t err[4];
-  TPC_HIP(hipMemcpyAsync(err, h.d.err, sizeof(err), hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipMemcpyAsync(event_track_off, h.d.ev_track_off, (ne + 1) * sizeof(uint32_t),
-                         hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipMemcpyAsync(event_hit_off, h.d.ev_hit_off, (ne + 1) * sizeof(uint32_t),
-                         hipMemcpyDeviceToHost, st));
-  TPC_HIP(hipStreamSynchronize(st));
+  const uint32_t* err;
+  const int rc = read_head(ctx, h.d.err, h.d.ev_track_off, h.d.ev_hit_off, ne + 1, &err);
+  if (rc) return rc;
+  const uint32_t *toff = err + 4, *hoff = toff + ne + 1;
+  // (on an error below the caller's arrays hold the offsets as read)
+  std::copy(toff, toff + ne + 1, event_track_off);
+  std::copy(hoff, hoff + ne + 1, event_hit_off);
   if (err[0]) return ctx->fail(TPC_EINVAL, std::to_string(err[0]) + " invalid clusters (sector, row or coordinates)");
   if (err[1]) return ctx->fail(TPC_EINVAL, "a pad row holds more than 4096 clusters");
   if (err[2]) return ctx->fail(TPC_EDEVICE, "internal capacity exceeded");
@@ -1260,6 +1306,7 @@ int tpc_destroy(tpc_ctx* ctx) {
     if (h.graph) (void)hipGraphExecDestroy(h.graph);
     if (h.done) (void)hipEventDestroy(h.done);
   }
+  if (ctx->head) (void)hipHostFree(ctx->head);
   delete ctx;
   return TPC_OK;
 }
@@ -1289,13 +1336,6 @@ struct StaticDevice {
 };
 StaticDevice g_static[kMaxStaticDevices];
 std::mutex g_static_mu;
-
-__global__ void k_static_stage(int64_t* ev_off, int64_t n) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    ev_off[0] = 0;
-    ev_off[1] = n;
-  }
-}
 
 // Tracks and hit IDs of the slot's one event into the caller's arrays (at
 // most max_tracks / max_hits of them) and the status words.
@@ -1397,7 +1437,10 @@ extern "C" int tpc_track_event_noalloc(const tpc_geometry* g, const tpc_params* 
   s.y = y;
   s.z = z;
   hipStream_t st = ctx->stream;
-  k_static_stage<<<1, 64, 0, st>>>(s.ev_off, n);
+  EventOffs o;
+  o.v[0] = 0;
+  o.v[1] = n;
+  k_event_off<<<1, 64, 0, st>>>(s.ev_off, o, 1);
   h.state = 1;
   int rc = build_grid(ctx, h);
   if (rc == TPC_OK) rc = track_range(ctx, h, 0, s.n_sectors);
