@@ -528,7 +528,7 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   const int nb_sel = (grid_stride_blocks(tl_bound * 32, 256, 2048) + 7) / 8 * 8;
   // a lane per hit of the range (the grid from the host bound; the kernel
   // strides over the device count)
-  launch_neighbours(ctx->p.win_batch, grid_stride_blocks(n_range, 256, 65536) / 8 * 8 + 8, st, s,
+  launch_neighbours(ctx->p.win_batch, grid_stride_blocks(n_range, 64, 262144) / 8 * 8 + 8, st, s,
                     ctx->k, g0, ns);
   if (marks) mark(ctx, 2);
   // a wave per pad row

@@ -6,7 +6,7 @@
 
 namespace tpc {
 
-constexpr int kNfThreads = 256;
+constexpr int kNfThreads = 64;
 
 __device__ __forceinline__ float nf_metric(float yd, float zd, float yu, float zu, float yh, float zh,
                                            float f, float wy, float wz) {
@@ -23,19 +23,20 @@ struct PairBest {
   uint32_t id_d = 0, id_u = 0;
   int32_t d = -1, u = -1;
   __device__ __forceinline__ void offer(float mm, uint32_t idd, uint32_t idu, int32_t pd, int32_t pu) {
-    const bool better = !have || mm < m || (mm == m && (idd < id_d || (idd == id_d && idu < id_u)));
-    if (better) {
-      have = true;
-      m = mm;
-      id_d = idd;
-      id_u = idu;
-      d = pd;
-      u = pu;
-    }
+    // (no branches: in a wave some lane takes each of them)
+    const bool less = mm < m, same = mm == m;
+    const bool id_less = idd < id_d, id_same = idd == id_d, idu_less = idu < id_u;
+    const bool better = !have | less | (same & (id_less | (id_same & idu_less)));
+    have = true;
+    m = better ? mm : m;
+    id_d = better ? idd : id_d;
+    id_u = better ? idu : id_u;
+    d = better ? pd : d;
+    u = better ? pu : u;
   }
 };
 
-constexpr int kNfCand = 32;      // up-row candidates listed per hit before a nested scan
+constexpr int kNfCand = 47;      // candidates of both rows listed per hit before a nested scan
 
 // a3: for each hit h of row r (1..157), the
 // pair (d in row r-1, u in row r+1) inside the origin-pointing windows
@@ -43,17 +44,27 @@ constexpr int kNfCand = 32;      // up-row candidates listed per hit before a ne
 // closest to h, measured by m = dy^2 / (1.5 sy^2) + dz^2 / (1.5 sz^2);
 // ties go to the smaller (id_d, id_u); the pair is kept if m <= m_max.
 // Rows 0 and 158 get no links.
-// One lane per hit.  The up-row candidates are listed once in LDS
-// (thread-minor, so a wave's accesses fall in distinct banks) and paired
-// with every down-row candidate as it is read; a hit with more than kNfCand
-// up candidates scans the up window again per down candidate.  Both rows
-// are read through the caches with the batched window reads (measured
-// faster than staging the rows in LDS, and than holding the candidates in
-// registers, whose fixed-length pairing loop costs more than it saves).
+// One lane per hit.  The candidates of both rows are listed in LDS
+// (thread-minor, so a wave's accesses fall in distinct banks; 16 bits each,
+// from the row's first hit: a row has at most 4096) and then paired; a hit
+// with more than kNfCand of them scans the up window for each down candidate.
+// Bound by instructions of waves whose lanes have lists of different lengths,
+// each wave issuing one in 8 cycles or so: hence waves on the SIMD count (6 by
+// registers and LDS; 4 waves to a block with 32-bit entries had 2.5), and so
+// does every branch.  A list is filled without one: each hit of the window's
+// bins is written to the next entry, which only a hit inside keeps.  Pairing
+// as each down hit is read ran the pair loop for every hit that any lane of
+// the wave had inside.
+// 15000 tracks 503 us: 16-bit entries 432, one-wave blocks 405, both rows
+// listed and no branches 262, registers for 6 waves 255 (64 events of 15000
+// tracks 3900, 3080, 2290, 2130; 2000 tracks 27.6, 22).  Measured best: 47
+// entries (63: 276; 32 for the up row alone, as before, and 16: 432 and 650),
+// 4 pairs at a time (1, 2, 8: 330, 286, 291).  Both rows are read through the
+// caches with the batched window reads (faster than staging the rows in LDS).
 // This function: sorted hit h, `my` the thread's candidate slots in LDS;
 // WB hit records are read per memory round trip (a tuning knob).
 template <int WB>
-__device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_t h, uint32_t* my) {
+__device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_t h, uint16_t* my) {
   const int sr = (int)S.hit_sr[h];
   const int g = sr / kRows;
   const int row = sr - g * kRows;
@@ -74,44 +85,55 @@ __device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_
   const float yh = x.y, zh = x.z;
   const float ypu = yh * rho_u, zpu = zh * rho_u;
   const float ypd = yh * rho_d, zpd = zh * rho_d;
+  // the candidates, up row first, then down row, as distances from the row's
+  // first hit; a hit past the list's end lands in the entry after it
   int nu = 0;
   for_window_hits<WB>(Bu, bou, S.hit, ypu, zpu, W, W, [&](uint32_t u, const Hit& c) {
-    if (!(fabsf(c.y - ypu) <= W && fabsf(c.z - zpu) <= W)) return;
-    if (nu < kNfCand) my[nu * kNfThreads] = u;
-    ++nu;
+    const bool in_y = fabsf(c.y - ypu) <= W, in_z = fabsf(c.z - zpu) <= W;
+    my[min(nu, kNfCand) * kNfThreads] = (uint16_t)(u - (uint32_t)Bu.first);
+    nu += in_y & in_z ? 1 : 0;
   });
   PairBest best;
   if (nu > 0) {
+    int nc = nu;
+    for_window_hits<WB>(Bd, bod, S.hit, ypd, zpd, W, W, [&](uint32_t d, const Hit& c) {
+      const bool in_y = fabsf(c.y - ypd) <= W, in_z = fabsf(c.z - zpd) <= W;
+      my[min(nc, kNfCand) * kNfThreads] = (uint16_t)(d - (uint32_t)Bd.first);
+      nc += in_y & in_z ? 1 : 0;
+    });
     const float sy = sigma_y(K, zh), sz = sigma_z(K, zh);
     const float wy = 1.0f / (1.5f * (sy * sy));
     const float wz = 1.0f / (1.5f * (sz * sz));
-    for_window_hits<WB>(Bd, bod, S.hit, ypd, zpd, W, W, [&](uint32_t d, const Hit& hd) {
-      if (!(fabsf(hd.y - ypd) <= W && fabsf(hd.z - zpd) <= W)) return;
-      if (nu <= kNfCand) {
-        // the listed up hits, WB records per memory round trip
+    if (nc <= kNfCand) {
+      for (int i = nu; i < nc; ++i) {
+        const uint32_t d = (uint32_t)Bd.first + my[i * kNfThreads];
+        const Hit hd = S.hit[d];
+        // WB records per memory round trip (the last one again past the end:
+        // a pair offered twice changes nothing)
         for (int k0 = 0; k0 < nu; k0 += WB) {
           uint32_t uu[WB];
           Hit hu[WB];
 #pragma unroll
-          for (int v = 0; v < WB; ++v)
-            if (k0 + v < nu) {
-              uu[v] = my[(k0 + v) * kNfThreads];
-              hu[v] = S.hit[uu[v]];
-            }
+          for (int v = 0; v < WB; ++v) {
+            uu[v] = (uint32_t)Bu.first + my[min(k0 + v, nu - 1) * kNfThreads];
+            hu[v] = S.hit[uu[v]];
+          }
 #pragma unroll
           for (int v = 0; v < WB; ++v)
-            if (k0 + v < nu)
-              best.offer(nf_metric(hd.y, hd.z, hu[v].y, hu[v].z, yh, zh, f, wy, wz), hd.id,
-                         hu[v].id, (int32_t)d, (int32_t)uu[v]);
+            best.offer(nf_metric(hd.y, hd.z, hu[v].y, hu[v].z, yh, zh, f, wy, wz), hd.id, hu[v].id,
+                       (int32_t)d, (int32_t)uu[v]);
         }
-      } else {
+      }
+    } else {
+      for_window_hits<WB>(Bd, bod, S.hit, ypd, zpd, W, W, [&](uint32_t d, const Hit& hd) {
+        if (!(fabsf(hd.y - ypd) <= W && fabsf(hd.z - zpd) <= W)) return;
         for_window_hits<WB>(Bu, bou, S.hit, ypu, zpu, W, W, [&](uint32_t u, const Hit& c) {
           if (!(fabsf(c.y - ypu) <= W && fabsf(c.z - zpu) <= W)) return;
           best.offer(nf_metric(hd.y, hd.z, c.y, c.z, yh, zh, f, wy, wz), hd.id, c.id,
                      (int32_t)d, (int32_t)u);
         });
-      }
-    });
+      });
+    }
   }
   const bool ok = best.have && best.m <= K.nf_mmax;
   S.up[h] = ok ? best.u : -1;
@@ -124,8 +146,8 @@ __device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_
 // contiguous eighth of the hits, so the rows r-1, r+1 its lanes read stay
 // in its L2.
 template <int WB>
-__global__ void __launch_bounds__(kNfThreads) k_neighbours(Slot S, DevConst K, int g0, int ns) {
-  __shared__ uint32_t cand[kNfCand * kNfThreads];
+__global__ void __launch_bounds__(kNfThreads, WB == 4 ? 6 : 1) k_neighbours(Slot S, DevConst K, int g0, int ns) {
+  __shared__ uint16_t cand[(kNfCand + 1) * kNfThreads];
   const uint32_t h_begin = S.row_off[g0 * kRows];
   const uint32_t h_end = S.row_off[(g0 + ns) * kRows];
   const uint32_t x = blockIdx.x % 8u, nbx = gridDim.x / 8u;
