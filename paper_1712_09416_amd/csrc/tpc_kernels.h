@@ -16,6 +16,7 @@ void launch_neighbours(int wb, int blocks, hipStream_t st, const Slot& S, const 
 // 566, 838, where two of the fp64 waves to a SIMD already share its issue)
 constexpr uint32_t kTrackletWaves = 2048;
 constexpr uint32_t kRefitWaves = 1024;
+constexpr uint32_t kFewTracklets = 2 * kTrackletWaves;     // 32 lanes or more a tracklet
 constexpr uint32_t kGroupTracklets = 8 * kTrackletWaves;   // eight lanes or more a tracklet
 // bound: the most tracklets there can be; blocks: for a lane a tracklet
 void launch_tracklets(int wb, int64_t bound, int blocks, int threads, hipStream_t st, const Slot& S,

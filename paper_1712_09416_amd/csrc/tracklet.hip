@@ -172,8 +172,11 @@ __device__ __forceinline__ bool try_hit(const DevConst& K, Helix<float>& h, cons
 // With these 60 tracks went from 397 to 362 us, 200 in one sector from 473 to
 // 436, 2000 from 761 to 703, 15000 from 1255 to 1180.
 // kGroup: a group of lg.size >= 8 lanes a tracklet, else a lane each (or a few
-// lanes, doing the same).
-template <int WB, bool kGroup>
+// lanes, doing the same).  kSearchFirst: at a row, those without a link to
+// follow search before the others try theirs, so that one update serves both;
+// a second one is for links that failed.  (A lane each: 1200 and 1249 us for
+// 15000 tracks, as some link of a wave fails at nearly every row.)
+template <int WB, bool kGroup, bool kSearchFirst>
 __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K, const RowRadii& R, int g0,
                                                uint32_t total, const LaneGroup& lg) {
   // Tracklets are ordered by (sector, row): give each XCD (blocks are
@@ -288,12 +291,22 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
         const float vy = sy * sy, vz = sz * sz;
         int32_t hit = next;
         bool got = false;
-        if (direct) got = try_hit(K, st, xg, vy, vz, tries);
-        if (!got) {
-          chain = false;
-          hit = kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xg)
-                       : search_row<WB>(S, K, rb, st, vy, vz, examined, xg);
+        if (kSearchFirst) {
+          if (!direct) hit = search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xg);
           if (hit >= 0) got = try_hit(K, st, xg, vy, vz, tries);
+          chain = direct & got;
+          if (direct & !got) {
+            hit = search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xg);
+            if (hit >= 0) got = try_hit(K, st, xg, vy, vz, tries);
+          }
+        } else {
+          if (direct) got = try_hit(K, st, xg, vy, vz, tries);
+          if (!got) {
+            chain = false;
+            hit = kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xg)
+                         : search_row<WB>(S, K, rb, st, vy, vz, examined, xg);
+            if (hit >= 0) got = try_hit(K, st, xg, vy, vz, tries);
+          }
         }
         block_push(blk, got ? (uint32_t)hit - first : (uint32_t)kNoEntry);
         pushed = r;
@@ -399,16 +412,31 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
         const float vy = sy * sy, vz = sz * sz;
         int32_t hit = uh;
         bool got = false;
-        if (uh >= 0) got = try_hit(K, st, xu, vy, vz, tries);
-        if (!got) {
-          Hit xs;
-          hit = kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xs)
-                       : search_row<WB>(S, K, rb, st, vy, vz, examined, xs);
+        if (kSearchFirst) {
+          Hit xs = xu;
+          if (uh < 0) hit = search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xs);
           if (hit >= 0) got = try_hit(K, st, xs, vy, vz, tries);
+          if ((uh >= 0) & !got) {
+            hit = search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xs);
+            if (hit >= 0) got = try_hit(K, st, xs, vy, vz, tries);
+          }
           if (!got) hit = -1;
-          if (hit != uh) {            // not what the outward phase found
+          if (hit != uh) {              // not what the outward phase found
             block_set(blk, r & 7, got ? (uint32_t)hit - first : (uint32_t)kNoEntry);
             dirty = true;
+          }
+        } else {
+          if (uh >= 0) got = try_hit(K, st, xu, vy, vz, tries);
+          if (!got) {
+            Hit xs;
+            hit = kGroup ? search_group(S, K, lg, first, nrow, rb, hx, st, vy, vz, examined, xs)
+                         : search_row<WB>(S, K, rb, st, vy, vz, examined, xs);
+            if (hit >= 0) got = try_hit(K, st, xs, vy, vz, tries);
+            if (!got) hit = -1;
+            if (hit != uh) {
+              block_set(blk, r & 7, got ? (uint32_t)hit - first : (uint32_t)kNoEntry);
+              dirty = true;
+            }
           }
         }
         if (got) {
@@ -498,34 +526,51 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
 // 2000 tracks 761 and 764; groups of 4 lanes were slower (2000 tracks in
 // 1.31 instead of 1.30 ms whole), as every search costs some 40 instructions
 // to bring the lanes' results together.
+// Of the first kernel there are two: with groups of 32 lanes or more (up to
+// kFewTracklets of them) a wave has one or two tracklets, and a link that is
+// followed needs no search; with smaller groups some tracklet of a wave
+// searches at nearly every row, and it costs less to let the others wait with
+// their update for it (32 events of 60 tracks 545 us, 480 so; 2000 tracks 708
+// and 662; 60 tracks, a wave each, 361 and 381).
+template <bool kSearchFirst>
 __global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g0) {
   __shared__ RowRadii R;
   const uint32_t total = S.range_cnt[0];
-  if (total > kGroupTracklets) return;
+  if (kSearchFirst ? total <= kFewTracklets || total > kGroupTracklets : total > kFewTracklets) return;
   load_radii(S, R);
   const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
-  make_tracklets<1, true>(S, K, R, g0, total, lg);
+  make_tracklets<1, true, kSearchFirst>(S, K, R, g0, total, lg);
 }
 
 template <int WB>
-__global__ void __launch_bounds__(256, WB == 8 ? 1 : 4) k_tracklets(Slot S, DevConst K, int g0) {
+__global__ void __launch_bounds__(256, WB == 8 ? 1 : 4) k_tracklets(Slot S, DevConst K, int g0,
+                                                                             uint32_t few) {
   __shared__ RowRadii R;
   const uint32_t total = S.range_cnt[0];
-  if (total <= kGroupTracklets) return;
+  if (total <= few) return;
   load_radii(S, R);
   const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
-  make_tracklets<WB, false>(S, K, R, g0, total, lg);
+  make_tracklets<WB, false, false>(S, K, R, g0, total, lg);
 }
 
+// The kernels whose counts the host's bound allows.  A bound of 32 times
+// kGroupTracklets or more leaves the first two out (few = 0, the last kernel
+// takes any count): clusters for that many start hits have given four times
+// kGroupTracklets, and an idle launch costs 5 us.
 void launch_tracklets(int wb, int64_t bound, int blocks, int threads, hipStream_t st, const Slot& S,
                       const DevConst& K, int g0) {
-  const int few = (int)std::min<int64_t>(kTrackletWaves * 64 / threads, (bound * 64 + threads - 1) / threads);
-  k_tracklets_few<<<(few + 7) / 8 * 8, threads, 0, st>>>(S, K, g0);
-  if (bound <= (int64_t)kGroupTracklets) return;
+  const uint32_t few = bound < 32 * (int64_t)kGroupTracklets ? kGroupTracklets : 0u;
+  if (few) {
+    const int64_t lanes = std::min<int64_t>(kTrackletWaves, bound) * 64;
+    const int nb = (int)((lanes + threads - 1) / threads + 7) / 8 * 8;
+    k_tracklets_few<false><<<nb, threads, 0, st>>>(S, K, g0);
+    if (bound > (int64_t)kFewTracklets) k_tracklets_few<true><<<nb, threads, 0, st>>>(S, K, g0);
+    if (bound <= (int64_t)few) return;
+  }
   switch (wb) {
-    case 2: k_tracklets<2><<<blocks, threads, 0, st>>>(S, K, g0); break;
-    case 8: k_tracklets<8><<<blocks, threads, 0, st>>>(S, K, g0); break;
-    default: k_tracklets<4><<<blocks, threads, 0, st>>>(S, K, g0); break;
+    case 2: k_tracklets<2><<<blocks, threads, 0, st>>>(S, K, g0, few); break;
+    case 8: k_tracklets<8><<<blocks, threads, 0, st>>>(S, K, g0, few); break;
+    default: k_tracklets<4><<<blocks, threads, 0, st>>>(S, K, g0, few); break;
   }
 }
 
