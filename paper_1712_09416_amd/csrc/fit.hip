@@ -338,7 +338,7 @@ __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int n
   const uint32_t c0 = min(total, xcd * chunk);
   const uint32_t c1 = min(total, c0 + chunk);
   unsigned nfit = 0;
-  const LaneGroup lg = lane_group(total, min(kRefitWaves, gridDim.x * (blockDim.x >> 6)));
+  const LaneGroup lg = lane_deal(total, min(kRefitWaves, gridDim.x * (blockDim.x >> 6)));
   const uint32_t waves = blockDim.x >> 6;
   for (uint32_t t = c0 + (jb * waves + (threadIdx.x >> 6)) * lg.per + lg.index; t < c1;
        t += nbx * waves * lg.per) {

@@ -209,7 +209,7 @@ __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot 
   load_radii(S, R);
   const uint32_t ntk = S.out_count[0];
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
-  const LaneGroup lg = lane_group(ntk, min(kRefitWaves, waves));
+  const LaneGroup lg = lane_deal(ntk, min(kRefitWaves, waves));
   const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   for (uint32_t a = wave * lg.per + lg.index; a < ntk; a += waves * lg.per) {
     const tpc_track& t = S.out_tracks[a];
@@ -725,7 +725,7 @@ __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot 
   load_radii(S, R);
   const uint32_t total = M.head_n[0];
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
-  const LaneGroup lg = lane_group(total, min(kRefitWaves, waves));
+  const LaneGroup lg = lane_deal(total, min(kRefitWaves, waves));
   const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   for (uint32_t i = wave * lg.per + lg.index; i < total; i += waves * lg.per) {
     const uint32_t a = (uint32_t)M.heads[i];

@@ -1,8 +1,8 @@
 // a5: tracklet construction (paper, Abstract: Kalman-filter track
-// following).  One lane per start hit, float arithmetic; the lane's state
-// and the decisions of its current block of 8 rows live in registers, its
-// hit list in global memory (row-indexed, a block written when the lane
-// leaves it).
+// following).  One lane per start hit, or a group of lanes where start hits
+// are few; float arithmetic; the lane's state and the decisions of its current
+// block of 8 rows live in registers, its hit list in global memory
+// (row-indexed, a block written when the lane leaves it).
 #include <algorithm>
 
 #include "tpc_device.h"
@@ -549,7 +549,7 @@ __global__ void __launch_bounds__(256, WB == 8 ? 1 : 4) k_tracklets(Slot S, DevC
   const uint32_t total = S.range_cnt[0];
   if (total <= few) return;
   load_radii(S, R);
-  const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
+  const LaneGroup lg = lane_deal(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
   make_tracklets<WB, false, false>(S, K, R, g0, total, lg);
 }
 
