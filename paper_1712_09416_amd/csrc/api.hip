@@ -423,13 +423,19 @@ int record_done(tpc_ctx* ctx, SlotHost& h) {
   return TPC_OK;
 }
 
+hipError_t alloc_head(tpc_ctx* ctx) {
+  const hipError_t e =
+      hipHostMalloc(reinterpret_cast<void**>(&ctx->head),
+                    (4 + 2 * ((size_t)ctx->p.max_events + 1)) * sizeof(uint32_t), hipHostMallocDefault);
+  if (e != hipSuccess) ctx->head = nullptr;
+  return e;
+}
+
 // k_read_head's words of n offsets each, read: host[0, 4) the errors, then the
 // track offsets, then the hit offsets
 int read_head(tpc_ctx* ctx, const uint32_t* err, const uint32_t* track_off, const uint32_t* hit_off, int n,
               const uint32_t** host) {
-  if (!ctx->head)
-    TPC_HIP(hipHostMalloc(reinterpret_cast<void**>(&ctx->head),
-                          (4 + 2 * ((size_t)ctx->p.max_events + 1)) * sizeof(uint32_t), hipHostMallocDefault));
+  if (!ctx->head) TPC_HIP(alloc_head(ctx));
   k_read_head<<<1, 256, 0, ctx->stream>>>(err, track_off, hit_off, n, ctx->head);
   TPC_LAUNCHED();
   TPC_HIP(hipStreamSynchronize(ctx->stream));
@@ -709,6 +715,9 @@ int tpc_init_geometry(tpc_ctx** out, const tpc_geometry* g, const tpc_params* p,
   ctx->slots.resize(p->max_slots);
   for (int i = 0; i < p->max_slots; ++i) carve_slot(c, *p, ctx->slots[i].d, &ctx->slots[i]);
   carve_lanes(c, *p, ctx->lanes);
+  // here, so that the first read-back allocates nothing (another thread may be
+  // capturing by then); without a GPU it stays for read_head to fail
+  if (alloc_head(ctx) != hipSuccess) (void)hipGetLastError();
   *out = ctx;
   return TPC_OK;
 }
