@@ -162,9 +162,7 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   s.row_off = c.take<uint32_t>(SR + 1);
   s.bins = c.take<RowBins>(SR);
   s.ev_tot = c.take<uint32_t>(SR + 1);
-  // a row of n hits has at most kBinsPerHit * max(n, 1) bins, plus one end entry;
-  // every row has room for that many (make_bins)
-  s.bin_off = c.take<uint32_t>(kBinsPerHit * (N + SR) + SR + 1);
+  s.bin_off = c.take<uint32_t>(bin_table_entries(N, SR));
   s.rank = c.take<uint32_t>(N);
   s.hit = c.take<Hit>(N);
   s.hit_sr = c.take<uint32_t>(N);

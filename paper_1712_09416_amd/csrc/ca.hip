@@ -75,8 +75,8 @@ __device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_
   }
   const RowBins Bd = S.bins[sr - 1], Bu = S.bins[sr + 1];
   const Hit x = S.hit[h];
-  const uint32_t* bod = S.bin_off + Bd.base;
-  const uint32_t* bou = S.bin_off + Bu.base;
+  const uint32_t* bod = bin_offsets(S, Bd);
+  const uint32_t* bou = bin_offsets(S, Bu);
   const float xd = S.row_x[row - 1], xr = S.row_x[row], xu = S.row_x[row + 1];
   const float rho_d = xd / xr;
   const float rho_u = xu / xr;

@@ -103,8 +103,7 @@ __global__ void __launch_bounds__(kCountThreads) k_count(Slot S) {
 // Bin layout of one row with n hits: ~bin_target hits per bin, edges at
 // least bin_min_edge, at most kBinsPerHit * max(n, 1) bins.
 // Its part of the bin table starts where the rows before it would end if all
-// were as long as they can be (row sr after `first` hits: two bins for every
-// hit and row, and an end entry a row), so no row waits for the others' layouts.
+// were as long as they can be, so no row waits for the others' layouts.
 __device__ RowBins make_bins(const DevConst& K, const Slot& S, int sr, uint32_t first, uint32_t n) {
   const int g = sr / kRows;
   const float x_row = S.row_x[sr - g * kRows];
@@ -133,7 +132,7 @@ __device__ RowBins make_bins(const DevConst& K, const Slot& S, int sr, uint32_t 
   b.nz = nz;
   b.iby = (float)ny / wy;
   b.ibz = (float)nz / wz;
-  b.base = (int32_t)((uint32_t)kBinsPerHit * (first + (uint32_t)sr) + (uint32_t)sr);
+  b.base = bin_table_pair(first, (uint32_t)sr);
   b.first = (int32_t)first;
   return b;
 }
@@ -407,7 +406,8 @@ __device__ __forceinline__ void sort_row(const Slot& S, const DevConst& K, int s
     S.hit[off + pos] = h[k];
     S.hit_sr[off + j] = (uint32_t)sr;
   }
-  for (int i = tid; i <= nb; i += T) S.bin_off[b.base + i] = off + L.hist[i];
+  uint32_t* bo = bin_offsets(S, b);
+  for (int i = tid; i <= nb; i += T) bo[i] = off + L.hist[i];
   sort_sync<T>();
 }
 
@@ -476,7 +476,8 @@ __global__ void __launch_bounds__(256) k_row_sort_large(Slot S, DevConst K) {
       S.hit[off + j] = h;
       S.hit_sr[off + j] = (uint32_t)sr;
     }
-    for (int i2 = threadIdx.x; i2 <= nb; i2 += blockDim.x) S.bin_off[b.base + i2] = off;
+    uint32_t* bo = bin_offsets(S, b);
+    for (int k = threadIdx.x; k <= nb; k += blockDim.x) bo[k] = off;
   }
 }
 

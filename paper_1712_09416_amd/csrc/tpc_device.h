@@ -15,6 +15,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "bin_table.h"
 #include "tpcca.h"
 
 namespace tpc {
@@ -22,7 +23,6 @@ namespace tpc {
 constexpr int kRows = 159;
 constexpr int kSectorsPerEvent = 36;
 constexpr int kMaxRowHits = 4096;         // LDS sort capacity of one pad row
-constexpr int kBinsPerHit = 2;            // a row has at most this many bins per hit
 constexpr uint32_t kNoHit = 0xFFFFFFFFu;
 constexpr int32_t kStartHit = -2;         // down link of a start hit
 constexpr int kRowBlocks = (kRows + 7) / 8;   // a tracklet's hit list in blocks of 8 rows
@@ -61,7 +61,7 @@ struct RowTable {
 struct RowBins {
   float y0, z0, iby, ibz;   // lower edges and inverse bin sizes
   int32_t ny, nz;           // bins in y and z
-  int32_t base;             // first entry of this row in bin_off
+  uint32_t base;            // first pair of entries of this row in bin_off (bin_table_pair)
   int32_t first;            // the row's first sorted hit
 };
 
@@ -92,7 +92,7 @@ struct Slot {
   uint32_t* row_off;        // [SR+1] first sorted hit of each (sector, row)
   RowBins* bins;            // [SR]
   uint32_t* ev_tot;         // [4 E] per event: hits, tracklet and track region entries, spare
-  uint32_t* bin_off;        // [2 (n + SR) + SR + 1] per row: its bins' first hits, then the end
+  uint32_t* bin_off;        // [2 (n + 2 SR)] per row: its bins' first hits, then the end
   uint32_t* rank;           // [n]
   Hit* hit;                 // [n] sorted by (sector, row, bin, id)
   uint32_t* hit_sr;         // [n] (sector, row) of each sorted hit (slot-wide index)
@@ -209,6 +209,10 @@ __device__ __forceinline__ void load_radii(const Slot& S, RowRadii& R) {
 // ---------------------------------------------------------------------------
 // pad-row bins: monotone in y and z, identical in every kernel
 // ---------------------------------------------------------------------------
+// the row's bin offset table (sorted-hit positions)
+__device__ __forceinline__ uint32_t* bin_offsets(const Slot& S, const RowBins& b) {
+  return S.bin_off + 2 * (size_t)b.base;
+}
 // (a NaN coordinate maps to bin 0: every index stays inside the row)
 __device__ __forceinline__ int bin_y(const RowBins& b, float y) {
   const float f = (y - b.y0) * b.iby;

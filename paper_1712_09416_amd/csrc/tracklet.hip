@@ -54,7 +54,7 @@ __device__ __forceinline__ int32_t search_row(const Slot& S, const DevConst& K, 
   int32_t best = -1;
   float bchi = 0.0f;
   uint32_t bid = 0;
-  for_window_hits<WB>(rb, S.bin_off + rb.base, S.hit, yc, zc, wy, wz, [&](uint32_t p, const Hit& x) {
+  for_window_hits<WB>(rb, bin_offsets(S, rb), S.hit, yc, zc, wy, wz, [&](uint32_t p, const Hit& x) {
     const float ry = x.y - yc, rz = x.z - zc;
     if (!(fabsf(ry) <= wy && fabsf(rz) <= wz)) return;
     ++examined;                 // hits inside the window (independent of the binning)
@@ -112,7 +112,7 @@ __device__ __forceinline__ int32_t search_group(const Slot& S, const DevConst& K
     const float eps = 1e-3f;
     const int iy0 = bin_y(rb, h.y - win.wy - eps), iy1 = bin_y(rb, h.y + win.wy + eps);
     const int iz0 = bin_z(rb, h.z - win.wz - eps), iz1 = bin_z(rb, h.z + win.wz + eps);
-    const uint32_t* bo = S.bin_off + rb.base;
+    const uint32_t* bo = bin_offsets(S, rb);
     for (int izb = iz0; izb <= iz1; izb += 4) {
       const int iz = izb + (int)(lg.lane & 3u);
       uint32_t lo = 0u, hi = 0u;
