@@ -19,10 +19,13 @@
  *  - Return codes: TPC_OK (0) or a negative TPC_E* code; tpc_last_error()
  *    gives a message.  Arguments are checked on the host before any device
  *    work is enqueued, so a failed call has enqueued nothing.
- *  - A context owns no device memory: the caller passes one device
+ *  - Making a context makes no HIP call, so it may be done while a stream is
+ *    captured.  A context owns no device memory: the caller passes one device
  *    workspace (e.g. a torch uint8 tensor's data pointer) of at least
  *    tpc_workspace_bytes() and a HIP stream; all work of the context is
- *    enqueued on that stream, in call order.  A context is not thread-safe.
+ *    enqueued on that stream, in call order.  Its first read of results takes
+ *    4 + 2 (max_events + 1) words of pinned host memory, which tpc_destroy
+ *    gives back.  A context is not thread-safe.
  *  - Cluster ID = index of the cluster in the event's input arrays; IDs must
  *    be < 2^24 per event.
  *  - Slots: a context has params->max_slots slots.  A slot holds one event

@@ -421,7 +421,17 @@ int record_done(tpc_ctx* ctx, SlotHost& h) {
   return TPC_OK;
 }
 
+// The calling thread's allocations neither refused by a stream capture in
+// progress (its own, or another thread's) nor ending it.
+struct BesideCaptures {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
+// At the first read-back, not when the context is made: that makes no HIP call.
 hipError_t alloc_head(tpc_ctx* ctx) {
+  BesideCaptures beside;
   const hipError_t e =
       hipHostMalloc(reinterpret_cast<void**>(&ctx->head),
                     (4 + 2 * ((size_t)ctx->p.max_events + 1)) * sizeof(uint32_t), hipHostMallocDefault);
@@ -713,9 +723,6 @@ int tpc_init_geometry(tpc_ctx** out, const tpc_geometry* g, const tpc_params* p,
   ctx->slots.resize(p->max_slots);
   for (int i = 0; i < p->max_slots; ++i) carve_slot(c, *p, ctx->slots[i].d, &ctx->slots[i]);
   carve_lanes(c, *p, ctx->lanes);
-  // here, so that the first read-back allocates nothing (another thread may be
-  // capturing by then); without a GPU it stays for read_head to fail
-  if (alloc_head(ctx) != hipSuccess) (void)hipGetLastError();
   *out = ctx;
   return TPC_OK;
 }
@@ -1314,7 +1321,10 @@ int tpc_destroy(tpc_ctx* ctx) {
     if (h.graph) (void)hipGraphExecDestroy(h.graph);
     if (h.done) (void)hipEventDestroy(h.done);
   }
-  if (ctx->head) (void)hipHostFree(ctx->head);
+  if (ctx->head) {
+    BesideCaptures beside;
+    (void)hipHostFree(ctx->head);
+  }
   delete ctx;
   return TPC_OK;
 }
