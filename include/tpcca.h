@@ -24,8 +24,9 @@
  *    workspace (e.g. a torch uint8 tensor's data pointer) of at least
  *    tpc_workspace_bytes() and a HIP stream; all work of the context is
  *    enqueued on that stream, in call order.  Its first read of results takes
- *    4 + 2 (max_events + 1) words of pinned host memory, which tpc_destroy
- *    gives back.  A context is not thread-safe.
+ *    a block of pinned host memory (33 KB), which tpc_destroy leaves to later
+ *    contexts (the library keeps at most 64 of them).  A context is not
+ *    thread-safe.
  *  - Cluster ID = index of the cluster in the event's input arrays; IDs must
  *    be < 2^24 per event.
  *  - Slots: a context has params->max_slots slots.  A slot holds one event

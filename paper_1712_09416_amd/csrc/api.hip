@@ -40,6 +40,8 @@ struct SlotHost {
 };
 
 // __global__ helpers local to this file
+constexpr int kMaxEvents = 4096;     // events of a slot
+
 // Event offsets of a slot that come as a kernel argument: up to 128 events (1
 // KB of arguments), of which each launch has room for 4.  A copy from the
 // host's vector is staged by the runtime, some 10 us of the caller's time.
@@ -280,7 +282,7 @@ void carve_lanes(Carver& c, const tpc_params& p, Lane* lanes) {
 bool params_ok(const tpc_params* p) {
   if (!p) return false;
   if (!(p->max_slots >= 1 && p->max_slots <= 1024)) return false;
-  if (!(p->max_events >= 1 && p->max_events <= 4096)) return false;
+  if (!(p->max_events >= 1 && p->max_events <= kMaxEvents)) return false;
   if (!(p->max_clusters >= 1 && p->max_clusters <= (int64_t)0x7FFFFFFF)) return false;
   if (!(p->n_gap >= 1 && p->n_min_tracklet >= 2 && p->n_min_track >= 3)) return false;
   if (!(p->n_min_chain >= 3 && p->n_min_chain <= kRows)) return false;
@@ -429,21 +431,50 @@ struct BesideCaptures {
   ~BesideCaptures() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
 };
 
-// At the first read-back, not when the context is made: that makes no HIP call.
-hipError_t alloc_head(tpc_ctx* ctx) {
+// Pinned blocks for read-backs, of one size (the largest slot's, 33 KB).  A
+// context takes one at its first read (not when it is made: that makes no HIP
+// call) and leaves it here for others: hipHostFree waits for everything on the
+// GPU (destroying a context beside 83 ms of another stream's work took these 83
+// ms, and takes 3 us so).  At most kHeadsKept are kept, until the process ends.
+constexpr size_t kHeadWords = 4 + 2 * (kMaxEvents + 1);
+constexpr int kHeadsKept = 64;
+std::mutex g_heads_mu;
+uint32_t* g_heads[kHeadsKept];
+int g_heads_n = 0;
+
+hipError_t take_head(uint32_t** head) {
+  {
+    std::lock_guard<std::mutex> lock(g_heads_mu);
+    if (g_heads_n > 0) {
+      *head = g_heads[--g_heads_n];
+      return hipSuccess;
+    }
+  }
   BesideCaptures beside;
-  const hipError_t e =
-      hipHostMalloc(reinterpret_cast<void**>(&ctx->head),
-                    (4 + 2 * ((size_t)ctx->p.max_events + 1)) * sizeof(uint32_t), hipHostMallocDefault);
-  if (e != hipSuccess) ctx->head = nullptr;
+  const hipError_t e = hipHostMalloc(reinterpret_cast<void**>(head), kHeadWords * sizeof(uint32_t),
+                                     hipHostMallocPortable);
+  if (e != hipSuccess) *head = nullptr;
   return e;
+}
+
+// idle: no read into it is still queued
+void leave_head(uint32_t* head, bool idle) {
+  if (idle) {
+    std::lock_guard<std::mutex> lock(g_heads_mu);
+    if (g_heads_n < kHeadsKept) {
+      g_heads[g_heads_n++] = head;
+      return;
+    }
+  }
+  BesideCaptures beside;
+  (void)hipHostFree(head);
 }
 
 // k_read_head's words of n offsets each, read: host[0, 4) the errors, then the
 // track offsets, then the hit offsets
 int read_head(tpc_ctx* ctx, const uint32_t* err, const uint32_t* track_off, const uint32_t* hit_off, int n,
               const uint32_t** host) {
-  if (!ctx->head) TPC_HIP(alloc_head(ctx));
+  if (!ctx->head) TPC_HIP(take_head(&ctx->head));
   k_read_head<<<1, 256, 0, ctx->stream>>>(err, track_off, hit_off, n, ctx->head);
   TPC_LAUNCHED();
   TPC_HIP(hipStreamSynchronize(ctx->stream));
@@ -1305,7 +1336,7 @@ const char* tpc_last_error(const tpc_ctx* ctx) {
 
 int tpc_destroy(tpc_ctx* ctx) {
   if (!ctx) return TPC_EINVAL;
-  (void)hipStreamSynchronize(ctx->stream);
+  const bool idle = hipStreamSynchronize(ctx->stream) == hipSuccess;
   for (auto& set : ctx->prof_ev)
     for (hipEvent_t e : set)
       if (e) (void)hipEventDestroy(e);
@@ -1321,10 +1352,7 @@ int tpc_destroy(tpc_ctx* ctx) {
     if (h.graph) (void)hipGraphExecDestroy(h.graph);
     if (h.done) (void)hipEventDestroy(h.done);
   }
-  if (ctx->head) {
-    BesideCaptures beside;
-    (void)hipHostFree(ctx->head);
-  }
+  if (ctx->head) leave_head(ctx->head, idle);
   delete ctx;
   return TPC_OK;
 }

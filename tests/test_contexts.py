@@ -111,3 +111,39 @@ def test_first_results_read_beside_another_threads_capture():
     again.close()
     assert len(tracks) >= 1 and np.array_equal(hits, want_hits)
     assert tracks.tobytes() == want_tracks.tobytes()
+
+
+@pytest.mark.gpu
+def test_destroying_a_context_waits_for_its_own_stream_only():
+    """Trackers read and closed while another stream works: that work is still
+    running afterwards; results read into blocks left by closed contexts are
+    the same, by several threads at once too."""
+    torch = pytest.importorskip("torch")
+    from paper_1712_09416_amd import Tracker
+    ev = tpcgen.tiny_event(7, n_tracks=4)
+    ins = [torch.from_numpy(a).to("cuda:0") for a in (ev.sector, ev.row, ev.y, ev.z)]
+
+    def one():
+        trk = Tracker(ev.geometry(), max_clusters=1 << 12)
+        trk.load(0, *ins)
+        trk.track_event(0)
+        tracks, hits = trk.get_tracks(0)
+        trk.close()
+        return tracks.tobytes() + hits.tobytes()
+
+    want = one()
+    other, done = torch.cuda.Stream(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(other):
+        torch.cuda._sleep(400_000_000)              # some 170 ms
+        done.record()
+    assert one() == want
+    assert not done.query()
+    torch.cuda.synchronize()
+    got = []
+    threads = [threading.Thread(target=lambda: got.extend(one() for _ in range(8))) for _ in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join(60)
+    assert got == [want] * 32
