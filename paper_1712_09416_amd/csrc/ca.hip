@@ -47,11 +47,17 @@ constexpr int kNfCand = 47;      // candidates of both rows listed per hit befor
 // One lane per hit.  The candidates of both rows are listed in LDS
 // (thread-minor, so a wave's accesses fall in distinct banks; 16 bits each,
 // from the row's first hit: a row has at most 4096) and then paired; a hit
-// with more than kNfCand of them scans the up window for each down candidate.
+// with more than kNfCand of them pairs the listed up row as it reads the down
+// row again, and scans the up window for each down candidate only if the up
+// row alone has more.  (Rows of 4096 hits spread over 8 sectors: 1.56 ms, 1.88
+// with that scan for every longer list, 2.50 with a list of 32 up hits; 1500
+// and a window of 5 cm: 0.49, 0.77, 0.74; 2000 in an eighth of two sectors,
+// where nearly every up row is too long: 12.2, 11.3, 12.5.)
 // Bound by instructions of waves whose lanes have lists of different lengths,
 // each wave issuing one in 8 cycles or so: hence waves on the SIMD count (6 by
 // registers and LDS; 4 waves to a block with 32-bit entries had 2.5), and so
-// does every branch.  A list is filled without one: each hit of the window's
+// does every branch.  (Nine registers are spilled for 6 waves: two of them once
+// a hit, the others in the scans of the longest lists.)  A list is filled without one: each hit of the window's
 // bins is written to the next entry, which only a hit inside keeps.  Pairing
 // as each down hit is read ran the pair loop for every hit that any lane of
 // the wave had inside.
@@ -104,26 +110,32 @@ __device__ __forceinline__ void nf_hit(const Slot& S, const DevConst& K, uint32_
     const float sy = sigma_y(K, zh), sz = sigma_z(K, zh);
     const float wy = 1.0f / (1.5f * (sy * sy));
     const float wz = 1.0f / (1.5f * (sz * sz));
+    // down hit d with the listed up hits, WB records per memory round trip (the
+    // last one again past the end: a pair offered twice changes nothing)
+    auto pair_listed = [&](uint32_t d, const Hit& hd) {
+      for (int k0 = 0; k0 < nu; k0 += WB) {
+        uint32_t uu[WB];
+        Hit hu[WB];
+#pragma unroll
+        for (int v = 0; v < WB; ++v) {
+          uu[v] = (uint32_t)Bu.first + my[min(k0 + v, nu - 1) * kNfThreads];
+          hu[v] = S.hit[uu[v]];
+        }
+#pragma unroll
+        for (int v = 0; v < WB; ++v)
+          best.offer(nf_metric(hd.y, hd.z, hu[v].y, hu[v].z, yh, zh, f, wy, wz), hd.id, hu[v].id,
+                     (int32_t)d, (int32_t)uu[v]);
+      }
+    };
     if (nc <= kNfCand) {
       for (int i = nu; i < nc; ++i) {
         const uint32_t d = (uint32_t)Bd.first + my[i * kNfThreads];
-        const Hit hd = S.hit[d];
-        // WB records per memory round trip (the last one again past the end:
-        // a pair offered twice changes nothing)
-        for (int k0 = 0; k0 < nu; k0 += WB) {
-          uint32_t uu[WB];
-          Hit hu[WB];
-#pragma unroll
-          for (int v = 0; v < WB; ++v) {
-            uu[v] = (uint32_t)Bu.first + my[min(k0 + v, nu - 1) * kNfThreads];
-            hu[v] = S.hit[uu[v]];
-          }
-#pragma unroll
-          for (int v = 0; v < WB; ++v)
-            best.offer(nf_metric(hd.y, hd.z, hu[v].y, hu[v].z, yh, zh, f, wy, wz), hd.id, hu[v].id,
-                       (int32_t)d, (int32_t)uu[v]);
-        }
+        pair_listed(d, S.hit[d]);
       }
+    } else if (nu <= kNfCand) {
+      for_window_hits<WB>(Bd, bod, S.hit, ypd, zpd, W, W, [&](uint32_t d, const Hit& hd) {
+        if (fabsf(hd.y - ypd) <= W && fabsf(hd.z - zpd) <= W) pair_listed(d, hd);
+      });
     } else {
       for_window_hits<WB>(Bd, bod, S.hit, ypd, zpd, W, W, [&](uint32_t d, const Hit& hd) {
         if (!(fabsf(hd.y - ypd) <= W && fabsf(hd.z - zpd) <= W)) return;

@@ -136,3 +136,27 @@ def test_many_clusters_few_tracklets(dev, oracle_lib):  # noqa: F811
     ref = oracle_run(oracle_lib, ev)
     compare_links(lk, ref)
     compare_tracks(tracks, hits, ref)
+
+
+# candidates of a hit in the rows above and below, around what its list holds
+# (47): both rows listed; the down row paired as it is read; neither listed
+@pytest.mark.parametrize("nu,nd", [(46, 1), (24, 23), (24, 24), (47, 1), (48, 1), (1, 46), (1, 47), (60, 60)])
+def test_neighbour_list_limits(dev, oracle_lib, nu, nd):  # noqa: F811
+    rng = np.random.default_rng(100 * nu + nd)
+    x = tpcgen.geometry.row_x().astype(np.float64)
+    cols = []
+    for sector in (2, 30):
+        for r in (1, 40, 63, 100, 150, 157):      # the middle row of three
+            side = 1.0 if sector < 18 else -1.0
+            for row, n in ((r - 1, nd), (r, 3), (r + 1, nu)):
+                # inside the window of every middle hit: 3 cm around the line
+                # from the origin
+                cols.append((np.full(n, sector), np.full(n, row), 0.05 * x[row] + rng.uniform(-1.2, 1.2, n),
+                             side * (0.6 * x[row] + rng.uniform(-1.2, 1.2, n))))
+    sector, row, y, z = [np.concatenate(c) for c in zip(*cols)]
+    order = rng.permutation(len(row))
+    ev = event(f"{nu} up, {nd} down", sector[order], row[order], y[order], z[order])
+    _, _, lk = gpu_run(ev, dev)
+    ref = oracle_run(oracle_lib, ev)
+    compare_links(lk, ref)
+    assert np.count_nonzero(lk["up"] >= 0) >= 12
