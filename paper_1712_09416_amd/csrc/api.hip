@@ -583,7 +583,8 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
            s.range_cnt + 0, false);
   k_start_write<<<nb_rows, 256, 0, st>>>(s, g0, ns);
   if (marks) mark(ctx, 3);
-  launch_tracklets(ctx->p.win_batch, tl_bound, nb_lane, ctx->p.tl_block, st, s, ctx->k, g0);
+  launch_tracklets(ctx->p.win_batch, tl_bound, n_range / ((int64_t)ns * kRows), nb_lane, ctx->p.tl_block, st,
+                   s, ctx->k, g0);
   if (marks) mark(ctx, 4);
   k_select<<<nb_sel, 256, 0, st>>>(s, ctx->k, g0);
   k_track_write<<<nb_sel, 256, 0, st>>>(s, g0, ns);
@@ -877,7 +878,8 @@ int tpc_merge(tpc_ctx* ctx, int slot, const tpc_merge_params* mp) {
   // blocks of four waves: a block's waves go to the four SIMDs of one CU, so
   // the working waves do not share SIMDs; a group of up to 64 lanes a track
   // where tracks are few, a lane a track where there are many
-  const int nbt = std::max(grid_stride_blocks(K, 256, 2048), grid_stride_blocks(K * 64, 256, kRefitWaves / 4));
+  const int nbt = std::max(grid_stride_blocks(K, 256, 2048),
+                           grid_stride_blocks(K * 64, 256, std::max(kOuterWaves, kChainWaves) / 4));
   const int nb = grid_stride_blocks(K, 256);
   const int64_t nsr = ns * kRows;
   k_mg_begin<<<grid_stride_blocks(std::max(nsr + 1, K), 256), 256, 0, st>>>(s, m);

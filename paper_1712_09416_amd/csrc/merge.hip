@@ -202,14 +202,14 @@ __device__ __forceinline__ const int32_t* track_hits(const Slot& S, const tpc_tr
 
 // M1, a lane group a track.  Bound like the refit: some 150 steps after one
 // another, each of some 330 instructions that a lone wave issues one by one
-// (2000 tracks 153 us with a lane a track, 142 so; 15000 tracks 160 either way,
-// where every wave has 32 of them).
+// (2000 tracks 153 us with a lane a track, 142 so on 1024 waves; 15000 tracks
+// 160 either way).
 __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot M, MergeConst C) {
   __shared__ RowRadii R;
   load_radii(S, R);
   const uint32_t ntk = S.out_count[0];
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
-  const LaneGroup lg = lane_deal(ntk, min(kRefitWaves, waves));
+  const LaneGroup lg = lane_deal(ntk, min(kOuterWaves, waves));
   const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   for (uint32_t a = wave * lg.per + lg.index; a < ntk; a += waves * lg.per) {
     const tpc_track& t = S.out_tracks[a];
@@ -725,7 +725,7 @@ __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot 
   load_radii(S, R);
   const uint32_t total = M.head_n[0];
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
-  const LaneGroup lg = lane_deal(total, min(kRefitWaves, waves));
+  const LaneGroup lg = lane_deal(total, min(kChainWaves, waves));
   const uint32_t wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   for (uint32_t i = wave * lg.per + lg.index; i < total; i += waves * lg.per) {
     const uint32_t a = (uint32_t)M.heads[i];

@@ -10,17 +10,41 @@ namespace tpc {
 // depend on it): wb = window hits read per round trip (2, 4, 8)
 void launch_neighbours(int wb, int blocks, hipStream_t st, const Slot& S, const DevConst& K, int g0,
                        int ns);
-// waves that few tracklets / tracks are spread over: measured best of 512,
-// 1024, 2048, 4096 (tracklets, us, 32 pp events: 824, 753, 714, 770; one
-// peripheral event: 809, 762, 755, 845; tracks: 334, 328, 611, 761; 354, 325,
-// 566, 838, where two of the fp64 waves to a SIMD already share its issue)
-constexpr uint32_t kTrackletWaves = 2048;
-constexpr uint32_t kRefitWaves = 1024;
-constexpr uint32_t kFewTracklets = 2 * kTrackletWaves;     // 32 lanes or more a tracklet
-constexpr uint32_t kGroupTracklets = 8 * kTrackletWaves;   // eight lanes or more a tracklet
-// bound: the most tracklets there can be; blocks: for a lane a tracklet
-void launch_tracklets(int wb, int64_t bound, int blocks, int threads, hipStream_t st, const Slot& S,
-                      const DevConst& K, int g0);
+// Waves that few tracklets (in lane groups, in lanes) and few tracks (refit;
+// the merger's outer fits and chains) are spread over.  A call by itself wants
+// more of them (its time is that of one wave's chain, and sparse waves are
+// shorter), calls in flight on several streams want fewer (a group's lanes do
+// the same work, so every wave more is issue that the others wait for).  The
+// line lies where calls in flight are not slower than with a lane an item; us
+// an event, alone and four in flight, with a lane an item, with 2048 / 2048 /
+// 1024 / 1024 / 1024 waves, which is best alone, and so:
+//   400 primaries     1540, 418    846, 370    857, 346
+//   1000              1540, 452   1028, 540   1090, 407
+//   2000              1541, 496   1157, 680   1202, 460
+//   4000              1660, 602   1264, 808   1330, 565
+//   32 events of 60   1715, 560   1068, 616   1073, 520
+//   merger, 2000      1223, 388    685, 376    692, 358
+//   merger, 6000      1088, 436    773, 487    788, 407
+// Groups where rows are short (a group of 8 tests one with a read a lane or
+// two, see short_row) are cheaper and the line is later: 7 events of 400 tracks
+// (the most: 15500 tracklets) 1663, 512; 1088, 660; 1092, 550.  32 events of 60
+// with a lane each 1278 alone, 617 with two in flight (1073, 582).
+// One step to either side, 2000 primaries: lanes on 1152 and 896 waves 1231,
+// 481 and 1220, 453; refit on 512 and 320: 1182, 483 and 1188, 455 (but 32
+// events of 60 up to 1150 alone with 320, by where its waves fall).  Groups on
+// 1536: 1550 primaries 1091, 498 (1588, 477 with a lane a tracklet).
+constexpr uint32_t kShortRowWaves = 2048;
+constexpr uint32_t kTrackletWaves = 1408;
+constexpr uint32_t kLaneWaves = 1024;
+constexpr uint32_t kRefitWaves = 384;
+constexpr uint32_t kOuterWaves = 512;
+constexpr uint32_t kChainWaves = 768;
+// tracklets of a wave with 32 lanes or more each, and with eight or more
+constexpr uint32_t kWideGroups = 2, kGroups = 8;
+// bound: the most tracklets there can be; row_hits: hits of a row on average;
+// blocks: for a lane a tracklet
+void launch_tracklets(int wb, int64_t bound, int64_t row_hits, int blocks, int threads, hipStream_t st,
+                      const Slot& S, const DevConst& K, int g0);
 // stage + grid
 __global__ void k_count(Slot S);
 __global__ void k_grid_begin(Slot S);

@@ -516,29 +516,30 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
   wave_add_u64(&S.stats[7], n_tries);
 }
 
-// A lane group a tracklet (up to kGroupTracklets of them) and a lane a
+// A lane group a tracklet (up to kGroups of them a wave) and a lane a
 // tracklet are two kernels: together they would need 145 registers, and the
 // second one four waves to a SIMD (at most 128: kept there by the launch
-// bound, at 9 spilled words outside of the rows' loops; 8 hits a read need 152).  Each leaves the other's
-// counts alone.  Where the line lies: with the 16384 tracklets or fewer of
-// this rule a group has 8 lanes or more.  A 60-track event 443 us by the
-// second kernel and 397 by this one, 200 tracks in one sector 496 and 473,
-// 2000 tracks 761 and 764; groups of 4 lanes were slower (2000 tracks in
+// bound, at 9 spilled words outside of the rows' loops; 8 hits a read need 152).
+// Each leaves the other's counts alone.  Where the line lies: on kTrackletWaves
+// or kShortRowWaves waves a group has 8 lanes or more.  A 60-track event 443 us
+// by the second kernel and 397 by this one, 200 tracks in one sector 496 and
+// 473, 2000 tracks 761 and 764; groups of 4 lanes were slower (2000 tracks in
 // 1.31 instead of 1.30 ms whole), as every search costs some 40 instructions
 // to bring the lanes' results together.
 // Of the first kernel there are two: with groups of 32 lanes or more (up to
-// kFewTracklets of them) a wave has one or two tracklets, and a link that is
+// kWideGroups of them a wave) a wave has one or two tracklets, and a link that is
 // followed needs no search; with smaller groups some tracklet of a wave
 // searches at nearly every row, and it costs less to let the others wait with
 // their update for it (32 events of 60 tracks 545 us, 480 so; 2000 tracks 708
 // and 662; 60 tracks, a wave each, 361 and 381).
 template <bool kSearchFirst>
-__global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g0) {
+__global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g0, uint32_t most) {
   __shared__ RowRadii R;
   const uint32_t total = S.range_cnt[0];
-  if (kSearchFirst ? total <= kFewTracklets || total > kGroupTracklets : total > kFewTracklets) return;
+  const uint32_t wide = kWideGroups * most;
+  if (kSearchFirst ? total <= wide || total > kGroups * most : total > wide) return;
   load_radii(S, R);
-  const LaneGroup lg = lane_group(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
+  const LaneGroup lg = lane_group(total, min(most, gridDim.x * (blockDim.x >> 6)));
   make_tracklets<1, true, kSearchFirst>(S, K, R, g0, total, lg);
 }
 
@@ -549,22 +550,23 @@ __global__ void __launch_bounds__(256, WB == 8 ? 1 : 4) k_tracklets(Slot S, DevC
   const uint32_t total = S.range_cnt[0];
   if (total <= few) return;
   load_radii(S, R);
-  const LaneGroup lg = lane_deal(total, min(kTrackletWaves, gridDim.x * (blockDim.x >> 6)));
+  const LaneGroup lg = lane_deal(total, min(kLaneWaves, gridDim.x * (blockDim.x >> 6)));
   make_tracklets<WB, false, false>(S, K, R, g0, total, lg);
 }
 
 // The kernels whose counts the host's bound allows.  A bound of 32 times
-// kGroupTracklets or more leaves the first two out (few = 0, the last kernel
-// takes any count): clusters for that many start hits have given four times
-// kGroupTracklets, and an idle launch costs 5 us.
-void launch_tracklets(int wb, int64_t bound, int blocks, int threads, hipStream_t st, const Slot& S,
-                      const DevConst& K, int g0) {
-  const uint32_t few = bound < 32 * (int64_t)kGroupTracklets ? kGroupTracklets : 0u;
+// theirs or more leaves the first two out (few = 0, the last kernel takes any
+// count): clusters for that many start hits have given four times as many as
+// they take, and an idle launch costs 5 us.
+void launch_tracklets(int wb, int64_t bound, int64_t row_hits, int blocks, int threads, hipStream_t st,
+                      const Slot& S, const DevConst& K, int g0) {
+  const uint32_t most = row_hits <= 2 * 64 / kGroups ? kShortRowWaves : kTrackletWaves;
+  const uint32_t few = bound < 32 * (int64_t)kGroups * most ? kGroups * most : 0u;
   if (few) {
-    const int64_t lanes = std::min<int64_t>(kTrackletWaves, bound) * 64;
+    const int64_t lanes = std::min<int64_t>(most, bound) * 64;
     const int nb = (int)((lanes + threads - 1) / threads + 7) / 8 * 8;
-    k_tracklets_few<false><<<nb, threads, 0, st>>>(S, K, g0);
-    if (bound > (int64_t)kFewTracklets) k_tracklets_few<true><<<nb, threads, 0, st>>>(S, K, g0);
+    k_tracklets_few<false><<<nb, threads, 0, st>>>(S, K, g0, most);
+    if (bound > (int64_t)kWideGroups * most) k_tracklets_few<true><<<nb, threads, 0, st>>>(S, K, g0, most);
     if (bound <= (int64_t)few) return;
   }
   switch (wb) {

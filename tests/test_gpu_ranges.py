@@ -160,3 +160,27 @@ def test_neighbour_list_limits(dev, oracle_lib, nu, nd):  # noqa: F811
     ref = oracle_run(oracle_lib, ev)
     compare_links(lk, ref)
     assert np.count_nonzero(lk["up"] >= 0) >= 12
+
+
+# groups of 64, 32, 16 and 8 lanes and a lane each, at the counts where the
+# next one takes over: three events of short chains (rows short on average,
+# 2048 waves), one of longer ones (rows of 17 hits or more, 1408 waves)
+@pytest.mark.parametrize("events,rows,n", [(3, 12, 2048), (3, 12, 2049), (3, 12, 4096), (3, 12, 4097),
+                                           (3, 12, 8192), (3, 12, 8193), (3, 12, 16384), (3, 12, 16385),
+                                           (1, 100, 1408), (1, 100, 1409), (1, 40, 2816), (1, 40, 2817),
+                                           (1, 20, 5632), (1, 20, 5633), (1, 12, 11264), (1, 12, 11265)])
+def test_lane_group_counts(dev, oracle_lib, events, rows, n):  # noqa: F811
+    from paper_1712_09416_amd import Tracker
+    evs = [chains((n + e) // events, rows) for e in range(events)]
+    offs = np.concatenate([[0], np.cumsum([ev.n for ev in evs])])
+    assert (offs[-1] // (events * 36 * 159) <= 16) == (events == 3)
+    cat = [np.concatenate([getattr(ev, k) for ev in evs]) for k in ("sector", "row", "y", "z")]
+    trk = Tracker(GEO, max_events=events, max_clusters=int(offs[-1]))
+    trk.set_profiling(True)
+    trk.load_batch(0, offs, *[torch.from_numpy(a).to(dev) for a in cat])
+    trk.track_event(0)
+    got = trk.get_slot_tracks(0)
+    assert trk.profile()[1]["tracklets"] == n
+    trk.close()
+    for ev, (tracks, hits) in zip(evs, got):
+        compare_tracks(tracks, hits, oracle_run(oracle_lib, ev))
