@@ -99,7 +99,7 @@ typedef struct tpc_params {
   /* launch shape (tuning only: the tracks never depend on these) */
   int32_t tl_block;         /* tracklet kernel threads per block: 64, 128 or 256 */
   int32_t win_batch;        /* window hits a lane reads per memory round trip: 2, 4 or 8 */
-  int32_t row_batch;        /* 4, 8 or 16; without effect (the selection's lanes take a row each) */
+  int32_t row_batch;        /* 4, 8 or 16; without effect */
 } tpc_params;
 
 /* One output track.  par / cov are given at x_ref, the pad-row radius of

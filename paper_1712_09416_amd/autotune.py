@@ -3,15 +3,16 @@
 The knobs change how the work is laid out, never what is computed: the
 pad-row grid's bin size (clusters per bin aimed at, smallest bin edge)
 changes how many hits each window query touches, never which hits pass the
-exact window test; the tracklet kernel's block size, the window hits read
-per memory round trip and the hit-list rows read per round trip by the
-selection change only the order of loads and lanes.  So the tracks do not
+exact window test; the tracklet kernel's block size and the window hits read
+per memory round trip change only the order of loads and lanes.  So the tracks do not
 depend on them: for a given batch the tuner times graph replays of each
 candidate, checks that its tracks are identical to the first candidate's,
 and keeps the fastest, one group of knobs at a time (coordinate descent).
 A candidate replaces the values held so far only when it is faster by more
 than a margin (1% by default, about the replays' run-to-run spread), so the
 shape does not wander between equally fast ones from run to run.
+`row_batch` is accepted and has no effect: candidates that differ in it alone
+are the same launch shape, timed once.
 """
 from __future__ import annotations
 
@@ -21,7 +22,7 @@ import itertools
 import numpy as np
 import torch
 
-from .tracker import Tracker
+from .tracker import Tracker, default_params, workspace_bytes
 
 KNOBS = {"bin_target": (0.25, 0.5, 1.0), "bin_min_edge": (1.0, 2.0, 3.0),
          "tl_block": (64, 128, 256), "win_batch": (2, 4, 8), "row_batch": (4, 8, 16)}
@@ -29,6 +30,7 @@ DEFAULTS = {"bin_target": 0.25, "bin_min_edge": 1.0, "tl_block": 64, "win_batch"
             "row_batch": 8}
 # groups tuned together, in this order
 GROUPS = (("bin_target", "bin_min_edge"), ("tl_block",), ("win_batch",), ("row_batch",))
+IDLE = ("row_batch",)         # knobs without effect
 
 
 def _digest(trk: Tracker, n_events: int) -> str:
@@ -56,11 +58,17 @@ def autotune(geometry: dict, offsets, sector, row, y, z, reps: int = 5, groups=G
     n_events = len(offs) - 1
     total = int(offs[-1])
     ms, ref = {}, None
+    by_shape = {}
 
     def run(cand):
         nonlocal ref
         label = _label(cand)
         if label in ms:
+            return ms[label]
+        shape = tuple(cand[k] for k in KNOBS if k not in IDLE)
+        if shape in by_shape:
+            workspace_bytes(default_params(max_events=n_events, max_clusters=total, **cand, **params))
+            ms[label] = by_shape[shape]
             return ms[label]
         trk = Tracker(geometry, max_events=n_events, max_clusters=total, **cand, **params)
         try:
@@ -80,7 +88,7 @@ def autotune(geometry: dict, offsets, sector, row, y, z, reps: int = 5, groups=G
                 trk.launch(0)
             e1.record(st)
             torch.cuda.synchronize()
-            ms[label] = e0.elapsed_time(e1) / reps
+            ms[label] = by_shape[shape] = e0.elapsed_time(e1) / reps
         finally:
             trk.close()
             del trk

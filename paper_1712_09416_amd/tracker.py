@@ -32,6 +32,14 @@ def default_params(**over) -> Params:
     return p
 
 
+def workspace_bytes(params: Params) -> int:
+    """Device bytes of a context's workspace; ValueError for invalid params."""
+    nbytes = _lib.load().tpc_workspace_bytes(ctypes.byref(params))
+    if nbytes == 0:
+        raise ValueError("invalid tracker parameters")
+    return nbytes
+
+
 def _ptr(t) -> int:
     if isinstance(t, torch.Tensor):
         return t.data_ptr()
@@ -52,9 +60,7 @@ class Tracker:
         self.params = default_params(max_slots=max_slots, max_events=max_events,
                                      max_clusters=int(max_clusters), **params)
         self.geometry = make_geometry(geometry)
-        nbytes = self.L.tpc_workspace_bytes(ctypes.byref(self.params))
-        if nbytes == 0:
-            raise ValueError("invalid tracker parameters")
+        nbytes = workspace_bytes(self.params)
         self.workspace = torch.empty(nbytes, dtype=torch.uint8, device=self.device)
         # a stream of its own (graph capture needs a non-default stream)
         self.stream = stream if stream is not None else torch.cuda.Stream(self.device)
