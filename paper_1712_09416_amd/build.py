@@ -31,14 +31,27 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
-def build(verbose: bool = False) -> str:
-    tmp = LIB + ".tmp"
-    cmd = [HIPCC, *FLAGS, "-o", tmp, *sources()]
+def compile_library(out: str, srcs: list, flags=(), verbose: bool = False) -> str:
+    tmp = out + ".tmp"
+    cmd = [HIPCC, *FLAGS, *flags, "-o", tmp, *srcs]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
-    os.replace(tmp, LIB)
-    return LIB
+    os.replace(tmp, out)
+    return out
+
+
+def build(verbose: bool = False) -> str:
+    return compile_library(LIB, sources(), verbose=verbose)
+
+
+# kernels that only the tests launch
+TEST_SRC = os.path.join(ROOT, "tests", "native", "roots.hip")
+TEST_LIB = os.path.join(ROOT, "tests", "native", "libroots.so")
+
+
+def build_tests(verbose: bool = False) -> str:
+    return compile_library(TEST_LIB, [TEST_SRC], flags=("-I", CSRC), verbose=verbose)
 
 
 if __name__ == "__main__":

@@ -376,7 +376,7 @@ template <> __device__ __forceinline__ double fabs_(double v) { return fabs(v); 
 template <class F> __device__ __forceinline__ F sqrt_(F v);
 template <> __device__ __forceinline__ float sqrt_(float v) { return sqrtf(v); }
 template <> __device__ __forceinline__ double sqrt_(double v) { return sqrt(v); }
-// Square root, reciprocal and quotient, correctly rounded, for operands that
+// Square root and reciprocal, correctly rounded, for operands that
 // the caller knows to be well inside the exponent range: the bits of sqrtf /
 // sqrt and of the division without the scaling and special-case steps that
 // the compiler adds around them (a filter step has four of these, and its
