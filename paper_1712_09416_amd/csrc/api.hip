@@ -163,7 +163,7 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   s.row_x = reinterpret_cast<const float*>(s.row_cnt);
   s.row_off = c.take<uint32_t>(SR + 1);
   s.bins = c.take<RowBins>(SR);
-  s.ev_tot = c.take<uint32_t>(SR + 1);
+  s.ev_tot = c.take<uint32_t>(4 * (int64_t)E);
   s.bin_off = c.take<uint32_t>(bin_table_entries(N, SR));
   s.rank = c.take<uint32_t>(N);
   s.hit = c.take<Hit>(N);
@@ -194,7 +194,7 @@ void carve_slot(Carver& c, const tpc_params& p, Slot& s, SlotHost* h) {
   s.tk_chi2 = c.take<double>(cap_tk);
   s.tmap = c.take<int32_t>(N);
   s.scan_a = c.take<uint32_t>(N + 1);
-  s.scan_b = c.take<uint32_t>(std::max<int64_t>(std::max<int64_t>(N, SR), cap_tl) / kScanTile + 4);
+  s.scan_b = c.take<uint32_t>(SR / kScanTile + 1);
   s.out_count = c.take<uint32_t>(2);
   s.out_ntk = c.take<uint32_t>(cap_tk + 1);
   s.out_order = c.take<int32_t>(cap_tk);
@@ -263,13 +263,11 @@ struct Lane {
 };
 
 void carve_lanes(Carver& c, const tpc_params& p, Lane* lanes) {
-  const int64_t N = p.max_clusters;
-  const int64_t S = (int64_t)p.max_events * kSectorsPerEvent;
-  const int64_t SR = S * kRows;
+  const int64_t SR = (int64_t)p.max_events * kSectorsPerEvent * kRows;
   const int64_t cap_tl = tracklet_cap(p);
   for (int i = 0; i < kMaxLanes; ++i) {
     uint32_t* a = c.take<uint32_t>(16);
-    uint32_t* b = c.take<uint32_t>(std::max<int64_t>(std::max<int64_t>(N, SR), cap_tl) / kScanTile + 4);
+    uint32_t* b = c.take<uint32_t>(SR / kScanTile + 1);
     uint32_t* t = c.take<uint32_t>(cap_tl + 1);
     if (lanes) {
       lanes[i].range_cnt = a;
@@ -487,23 +485,19 @@ int grid_stride_blocks(int64_t n, int threads, int cap = 4096) {
   return (int)std::max<int64_t>(1, std::min<int64_t>(b, cap));
 }
 
-// Exclusive scan in place of data[0, n) (n = *n_dev if given, else n_bound,
-// which bounds it); the total goes to total_out and, with write_end, to
-// data[n].
-void scan_u32(hipStream_t st, uint32_t* data, const uint32_t* n_dev, int64_t n_bound,
-              uint32_t* partial, uint32_t* total_out, bool write_end = true) {
-  if (n_bound <= kSmallScanMax) {
-    k_scan_small<<<1, 1024, 0, st>>>(data, n_dev, n_bound, total_out, write_end ? 1 : 0);
+// Exclusive scan in place of data[0, n), n at most the rows of the slot; the
+// total goes to total_out (if given) and, with write_end, to data[n].
+void scan_u32(hipStream_t st, uint32_t* data, int64_t n, uint32_t* partial, uint32_t* total_out,
+              bool write_end = true) {
+  if (n <= kSmallScanMax) {
+    k_scan_small<<<1, 1024, 0, st>>>(data, (uint32_t)n, total_out, write_end ? 1 : 0);
     return;
   }
-  const int nb = (int)std::max<int64_t>(1, (n_bound + kScanTile - 1) / kScanTile);
-  k_scan_tiles<<<nb, 256, 0, st>>>(data, n_dev, n_bound, partial);
-  k_scan_partials<<<1, 1024, 0, st>>>(partial, nb, data, n_dev, n_bound, total_out,
-                                      write_end ? 1 : 0);
-  k_scan_apply<<<nb, 256, 0, st>>>(data, n_dev, n_bound, partial, data);
+  const int nb = (int)((n + kScanTile - 1) / kScanTile);
+  k_scan_tiles<<<nb, 256, 0, st>>>(data, (uint32_t)n, partial);
+  k_scan_partials<<<1, 1024, 0, st>>>(partial, nb, data, (uint32_t)n, total_out, write_end ? 1 : 0);
+  k_scan_apply<<<nb, 256, 0, st>>>(data, (uint32_t)n, partial);
 }
-
-
 
 int build_grid(tpc_ctx* ctx, SlotHost& h) {
   Slot& s = h.d;
@@ -515,9 +509,9 @@ int build_grid(tpc_ctx* ctx, SlotHost& h) {
   const unsigned chunks = (unsigned)((max_ev + kCountChunkHost - 1) / kCountChunkHost);
   k_count<<<dim3(chunks, h.n_events), 256, 0, st>>>(s);
   if (h.n_events > 1)
-    k_rows<true><<<h.n_events, kRowThreadsLaunch, 0, st>>>(s, ctx->x, ctx->p.n_min_chain,
+    k_rows<true><<<h.n_events, kRowThreads, 0, st>>>(s, ctx->x, ctx->p.n_min_chain,
                                                            ctx->p.n_min_track);
-  k_rows<false><<<h.n_events, kRowThreadsLaunch, 0, st>>>(s, ctx->x, ctx->p.n_min_chain,
+  k_rows<false><<<h.n_events, kRowThreads, 0, st>>>(s, ctx->x, ctx->p.n_min_chain,
                                                           ctx->p.n_min_track);
   const int64_t flat = (h.n + kCountChunkHost - 1) / kCountChunkHost;
   k_scatter<<<(unsigned)std::max<int64_t>(8, (flat + 7) / 8 * 8), 256, 0, st>>>(s);
@@ -579,8 +573,7 @@ int track_range(tpc_ctx* ctx, SlotHost& h, int g0, int ns, const Lane* lane = nu
   // a wave per pad row
   const int nb_rows = grid_stride_blocks((int64_t)ns * kRows * 64, 256, 16384);
   k_clean_rows<<<nb_rows, 256, 0, st>>>(s, g0, ns, ctx->p.n_min_chain);
-  scan_u32(st, s.row_nstart + (size_t)g0 * kRows, nullptr, (int64_t)ns * kRows, s.scan_b,
-           s.range_cnt + 0, false);
+  scan_u32(st, s.row_nstart + (size_t)g0 * kRows, (int64_t)ns * kRows, s.scan_b, s.range_cnt + 0, false);
   k_start_write<<<nb_rows, 256, 0, st>>>(s, g0, ns);
   if (marks) mark(ctx, 3);
   launch_tracklets(ctx->p.win_batch, tl_bound, n_range / ((int64_t)ns * kRows), nb_lane, ctx->p.tl_block, st,
@@ -884,7 +877,7 @@ int tpc_merge(tpc_ctx* ctx, int slot, const tpc_merge_params* mp) {
   const int64_t nsr = ns * kRows;
   k_mg_begin<<<grid_stride_blocks(std::max(nsr + 1, K), 256), 256, 0, st>>>(s, m);
   k_mg_count<<<nb, 256, 0, st>>>(s, m);
-  scan_u32(st, m.in_off, nullptr, nsr, s.scan_b, nullptr);
+  scan_u32(st, m.in_off, nsr, s.scan_b, nullptr);
   k_mg_scatter<<<nb, 256, 0, st>>>(s, m);
   k_mg_outer<<<nbt, 256, 0, st>>>(s, ctx->k, m, C);
   // one-wave blocks, four tracks each
@@ -903,7 +896,7 @@ int tpc_merge(tpc_ctx* ctx, int slot, const tpc_merge_params* mp) {
   k_mg_emit<<<nbo, 256, 0, st>>>(s, m, chunk);
   k_mg_pos<<<nbo, 256, 0, st>>>(s, m, chunk);
   // 16 lanes a track
-  k_mg_write<<<grid_stride_blocks(K * 16, 256, 4096), 256, 0, st>>>(s, ctx->k, m);
+  k_mg_write<<<grid_stride_blocks(K * 16, 256, 4096), 256, 0, st>>>(s, m);
   TPC_LAUNCHED();
   h.merged = true;
   return record_done(ctx, h);

@@ -252,7 +252,7 @@ __global__ void __launch_bounds__(kSelThreads) k_track_write(Slot S, int g0, int
 // True: st is the state after the update with own[jmin], where the walk
 // ends.  False: a transport failed below the hit jlast, the last one
 // updated; st is of no use then.  Memory reads are issued ahead of their use.
-__device__ __forceinline__ bool refit_walk(const Slot& S, const DevConst& K, const RowRadii& R, const int32_t* own,
+__device__ __forceinline__ bool refit_walk(const Slot& S, const DevConst& K, const RowTable& R, const int32_t* own,
                                            const uint8_t* own_row, int n, int jmin, double s0,
                                            double t0, double q0, Helix<double>& st, double& chi2,
                                            int& jlast) {
@@ -308,7 +308,7 @@ __device__ __forceinline__ bool refit_walk(const Slot& S, const DevConst& K, con
 // there is not kept on the way (20 doubles copied at every update, a seventh
 // of a step's instructions, for the few tracks that need it): the walk is
 // made again down to that hit, by the same arithmetic, and so ends there.
-__device__ __forceinline__ void refit_pass(const Slot& S, const DevConst& K, const RowRadii& R, const int32_t* own,
+__device__ __forceinline__ void refit_pass(const Slot& S, const DevConst& K, const RowTable& R, const int32_t* own,
                                            const uint8_t* own_row, int n, int& jmin, double s0,
                                            double t0, double q0, Helix<double>& st, double& chi2) {
   int jlast;
@@ -323,7 +323,7 @@ __device__ __forceinline__ void refit_pass(const Slot& S, const DevConst& K, con
 // at the innermost fitted hit; its cluster is marked for the canonical
 // ordering.
 __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int ns) {
-  __shared__ RowRadii R;
+  __shared__ RowTable R;
   load_radii(S, R);
   const uint32_t tk0 = S.tk_base[g0];
   // tracks past the region were not written (capacity error raised)
@@ -349,7 +349,6 @@ __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int n
     const int32_t* own = S.tk_own + (size_t)k * kRows;
     const uint8_t* own_row = S.tk_own_row + (size_t)k * kRows;
     int32_t* out = S.tk_info + (size_t)k * 4;
-    out[0] = 0;
     if (n < 1) continue;
     const int ro = own_row[n - 1];
     const int rin_tl = S.tl_info[(size_t)T * 4 + 1];
@@ -376,7 +375,6 @@ __global__ void __launch_bounds__(256) k_refit(Slot S, DevConst K, int g0, int n
     }
     const int nfitted = n - jmin;
     if (!ok || nfitted < K.n_min_track || !lg.first) continue;
-    out[0] = 1;
     out[1] = nfitted;
     out[2] = rin;
     out[3] = ro;

@@ -150,7 +150,6 @@ __global__ void k_grid_begin(Slot S) {
 
 // Running sum over a block of kRowThreads threads (exclusive, in place);
 // returns the block's total.
-constexpr int kRowThreads = 1024;
 constexpr int kRowsOfThread = (kEventRows + kRowThreads - 1) / kRowThreads;
 __device__ __forceinline__ uint32_t row_block_scan(uint32_t& v) {
   __shared__ uint32_t ws[kRowThreads / 64];

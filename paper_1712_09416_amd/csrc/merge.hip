@@ -40,7 +40,7 @@ namespace tpc {
 
 constexpr int kMaxChain = 16;    // segments of one chain (each holds >= 10 of the 159 rows)
 
-__device__ __forceinline__ double xrow(const RowRadii& R, int r) { return (double)R.x[r]; }
+__device__ __forceinline__ double xrow(const RowTable& R, int r) { return (double)R.x[r]; }
 
 __device__ __forceinline__ void prior_d(const DevConst& K, Helix<double>& st, double zv) {
   const double sy = (double)K.sy0 + K.sy1zd * fabs(zv);
@@ -205,7 +205,7 @@ __device__ __forceinline__ const int32_t* track_hits(const Slot& S, const tpc_tr
 // (2000 tracks 153 us with a lane a track, 142 so on 1024 waves; 15000 tracks
 // 160 either way).
 __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot M, MergeConst C) {
-  __shared__ RowRadii R;
+  __shared__ RowTable R;
   load_radii(S, R);
   const uint32_t ntk = S.out_count[0];
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
@@ -567,7 +567,7 @@ struct Chain {
 // changes, which fall at different rows for different chains (a loop over
 // segments with a row loop inside would hold every lane of a wave in each
 // segment until the longest one of the wave ends).
-__device__ bool chain_pass(const Slot& S, const DevConst& K, const RowRadii& R, const MergeConst& C, const Chain& ch,
+__device__ bool chain_pass(const Slot& S, const DevConst& K, const RowTable& R, const MergeConst& C, const Chain& ch,
                            double s0, double t0, double q0, Helix<double>& out, double& chi2,
                            int& n) {
   const int64_t ev0 = ch.ev0;
@@ -688,7 +688,7 @@ __device__ bool chain_pass(const Slot& S, const DevConst& K, const RowRadii& R, 
 // pass resets the covariance, so only its parameters matter): through each
 // segment to its last row in equal steps of at most step_max, turning
 // frames between segments; one flat loop of steps, as the pass.
-__device__ bool carry_out(const DevConst& K, const RowRadii& R, const MergeConst& C, const Chain& ch,
+__device__ bool carry_out(const DevConst& K, const RowTable& R, const MergeConst& C, const Chain& ch,
                           Helix<double> st, double& s0, double& t0, double& q0) {
   double x = xrow(R, ch.rin[0]);
   int j = 0;
@@ -721,7 +721,7 @@ __device__ bool carry_out(const DevConst& K, const RowRadii& R, const MergeConst
 // no heads idle, left 1 to 10 lanes of a wave at work, which then issues at
 // half the rate: 2000 tracks 692 us, now 526; 15000 tracks 702, now 632.
 __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot M, MergeConst C) {
-  __shared__ RowRadii R;
+  __shared__ RowTable R;
   load_radii(S, R);
   const uint32_t total = M.head_n[0];
   const uint32_t waves = gridDim.x * (blockDim.x >> 6);
@@ -882,7 +882,7 @@ __device__ __forceinline__ void copy_hits(int32_t* dst, const int32_t* src, int 
 // Merged tracks and their hits, kWriteLanes lanes a track (a lane by itself
 // touches a line of its own with every word: 2000 tracks 45 us, now 24; 15000
 // tracks 55, now 43), and the per-event ranges.
-__global__ void __launch_bounds__(256) k_mg_write(Slot S, DevConst K, MergeSlot M) {
+__global__ void __launch_bounds__(256) k_mg_write(Slot S, MergeSlot M) {
   const uint32_t ntk = S.out_count[0];
   const uint32_t first = blockIdx.x * blockDim.x + threadIdx.x;
   const uint32_t stride = gridDim.x * blockDim.x;

@@ -12,26 +12,20 @@ constexpr int kScanPerThread = 4;
 constexpr int kScanBlock = 256;
 constexpr int kScanTile = kScanBlock * kScanPerThread;
 
-__device__ __forceinline__ uint32_t scan_n(const uint32_t* n_dev, int64_t n_host) {
-  return n_dev ? *n_dev : (uint32_t)n_host;
-}
-
-__global__ void __launch_bounds__(kScanBlock) k_scan_tiles(const uint32_t* in, const uint32_t* n_dev,
-                                                           int64_t n_host, uint32_t* partial) {
-  const uint32_t n = scan_n(n_dev, n_host);
+__global__ void __launch_bounds__(kScanBlock) k_scan_tiles(const uint32_t* data, uint32_t n,
+                                                           uint32_t* partial) {
   const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanPerThread;
   uint32_t s = 0;
 #pragma unroll
   for (int j = 0; j < kScanPerThread; ++j)
-    if (base + j < n) s += in[base + j];
+    if (base + j < n) s += data[base + j];
   uint32_t ex;
   const uint32_t tot = block_scan256(s, &ex);
   if (threadIdx.x == 0) partial[blockIdx.x] = tot;
 }
 
-__global__ void __launch_bounds__(1024) k_scan_partials(uint32_t* partial, int nb, uint32_t* out,
-                                                        const uint32_t* n_dev, int64_t n_host,
-                                                        uint32_t* total_out, int write_end) {
+__global__ void __launch_bounds__(1024) k_scan_partials(uint32_t* partial, int nb, uint32_t* data,
+                                                        uint32_t n, uint32_t* total_out, int write_end) {
   __shared__ uint32_t w[32];
   __shared__ uint32_t carry;
   if (threadIdx.x == 0) carry = 0;
@@ -54,21 +48,18 @@ __global__ void __launch_bounds__(1024) k_scan_partials(uint32_t* partial, int n
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    const uint32_t n = scan_n(n_dev, n_host);
-    if (write_end) out[n] = carry;
+    if (write_end) data[n] = carry;
     if (total_out) *total_out = carry;
   }
 }
 
-// Whole scan in one 1024-thread block for n <= kSmallScanMax (the per-row
-// and per-sector tables): each thread scans a contiguous run of
+// Whole scan in one 1024-thread block for n <= kSmallScanMax (the rows of one
+// or two events): each thread scans a contiguous run of
 // kSmallPerThread values in registers.  In place; writes the total to
 // data[n] (write_end) and *total_out (if given).
-__global__ void __launch_bounds__(1024) k_scan_small(uint32_t* data, const uint32_t* n_dev,
-                                                     int64_t n_host, uint32_t* total_out,
+__global__ void __launch_bounds__(1024) k_scan_small(uint32_t* data, uint32_t n, uint32_t* total_out,
                                                      int write_end) {
   __shared__ uint32_t ws[16];
-  const uint32_t n = scan_n(n_dev, n_host);
   const uint32_t base = threadIdx.x * kSmallPerThread;
   uint32_t v[kSmallPerThread];
   uint32_t s = 0;
@@ -99,17 +90,15 @@ __global__ void __launch_bounds__(1024) k_scan_small(uint32_t* data, const uint3
   }
 }
 
-// in-place capable: each thread reads its values before writing them
-__global__ void __launch_bounds__(kScanBlock) k_scan_apply(const uint32_t* in, const uint32_t* n_dev,
-                                                           int64_t n_host, const uint32_t* partial,
-                                                           uint32_t* out) {
-  const uint32_t n = scan_n(n_dev, n_host);
+// in place: each thread reads its values before writing them
+__global__ void __launch_bounds__(kScanBlock) k_scan_apply(uint32_t* data, uint32_t n,
+                                                           const uint32_t* partial) {
   const uint64_t base = (uint64_t)blockIdx.x * kScanTile + (uint64_t)threadIdx.x * kScanPerThread;
   uint32_t v[kScanPerThread];
   uint32_t s = 0;
 #pragma unroll
   for (int j = 0; j < kScanPerThread; ++j) {
-    v[j] = (base + j < n) ? in[base + j] : 0u;
+    v[j] = (base + j < n) ? data[base + j] : 0u;
     s += v[j];
   }
   uint32_t ex;
@@ -117,7 +106,7 @@ __global__ void __launch_bounds__(kScanBlock) k_scan_apply(const uint32_t* in, c
   uint32_t run = partial[blockIdx.x] + ex;
 #pragma unroll
   for (int j = 0; j < kScanPerThread; ++j) {
-    if (base + j < n) out[base + j] = run;
+    if (base + j < n) data[base + j] = run;
     run += v[j];
   }
 }

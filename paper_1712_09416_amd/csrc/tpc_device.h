@@ -120,14 +120,14 @@ struct Slot {
   int32_t* tk_own;          // [tk capacity][kRows] owned hits (sorted index), ascending row
   uint8_t* tk_own_row;      // [tk capacity][kRows] their rows
   int32_t* tk_nown;         // [tk capacity]
-  int32_t* tk_info;         // [tk capacity][4]: ok, n, row_in, row_out
+  int32_t* tk_info;         // [tk capacity][4]: spare, n, row_in, row_out (fitted tracks only)
   double* tk_par;           // [tk capacity][5]
   double* tk_cov;           // [tk capacity][15]
   double* tk_chi2;          // [tk capacity]
   // canonical order
   int32_t* tmap;            // [n] per global cluster: temp track whose innermost hit it is
   uint32_t* scan_a;         // [n+1] scratch: the output order's counts per stretch of clusters
-  uint32_t* scan_b;         // [block partials]
+  uint32_t* scan_b;         // [SR / scan tile + 1] block partials of a scan over rows
   uint32_t* out_count;      // [2]: tracks, hits of the slot
   uint32_t* out_ntk;        // [tk capacity+1] first hit of each track, in canonical order
   int32_t* out_order;       // [tk capacity] temporary track of each canonical position
@@ -198,10 +198,7 @@ __device__ __forceinline__ int32_t entry_hit(uint32_t e, uint32_t first) {
 }
 
 // the pad-row radii in LDS, for the kernels that walk the rows
-struct RowRadii {
-  float x[kRows + 1];
-};
-__device__ __forceinline__ void load_radii(const Slot& S, RowRadii& R) {
+__device__ __forceinline__ void load_radii(const Slot& S, RowTable& R) {
   for (int r = threadIdx.x; r < kRows; r += blockDim.x) R.x[r] = S.row_x[r];
   __syncthreads();
 }

@@ -48,6 +48,7 @@ void launch_tracklets(int wb, int64_t bound, int64_t row_hits, int blocks, int t
 // stage + grid
 __global__ void k_count(Slot S);
 __global__ void k_grid_begin(Slot S);
+constexpr int kRowThreads = 1024;   // threads of k_rows
 template <bool kTotals>
 __global__ void k_rows(Slot S, RowTable X, int n_min_chain, int n_min_track);
 __global__ void k_scatter(Slot S);
@@ -62,17 +63,13 @@ __global__ void k_track_write(Slot S, int g0, int ns);
 // Kalman filter
 __global__ void k_refit(Slot S, DevConst K, int g0, int ns);
 // output
-__global__ void k_scan_tiles(const uint32_t* in, const uint32_t* n_dev, int64_t n_host,
-                             uint32_t* partial);
-__global__ void k_scan_partials(uint32_t* partial, int nb, uint32_t* out, const uint32_t* n_dev,
-                                int64_t n_host, uint32_t* total_out, int write_end);
-__global__ void k_scan_apply(const uint32_t* in, const uint32_t* n_dev, int64_t n_host,
-                             const uint32_t* partial, uint32_t* out);
-constexpr int kRowThreadsLaunch = 1024;   // threads of k_rows
+__global__ void k_scan_tiles(const uint32_t* data, uint32_t n, uint32_t* partial);
+__global__ void k_scan_partials(uint32_t* partial, int nb, uint32_t* data, uint32_t n, uint32_t* total_out,
+                                int write_end);
+__global__ void k_scan_apply(uint32_t* data, uint32_t n, const uint32_t* partial);
 constexpr int kSmallPerThread = 16;
 constexpr int64_t kSmallScanMax = 1024 * kSmallPerThread;
-__global__ void k_scan_small(uint32_t* data, const uint32_t* n_dev, int64_t n_host,
-                             uint32_t* total_out, int write_end);
+__global__ void k_scan_small(uint32_t* data, uint32_t n, uint32_t* total_out, int write_end);
 constexpr int kOrderBlocks = 2048;
 constexpr int kOrderTile = 1024;    // clusters a block of the output order takes at a time
 __global__ void k_out_count(Slot S, int64_t chunk);
@@ -90,7 +87,7 @@ __global__ void k_mg_link(Slot S, MergeSlot M);
 __global__ void k_mg_chain(Slot S, DevConst K, MergeSlot M, MergeConst C);
 __global__ void k_mg_emit(Slot S, MergeSlot M, int64_t chunk);
 __global__ void k_mg_pos(Slot S, MergeSlot M, int64_t chunk);
-__global__ void k_mg_write(Slot S, DevConst K, MergeSlot M);
+__global__ void k_mg_write(Slot S, MergeSlot M);
 // drift-velocity calibration
 __global__ void k_cal_accumulate(Slot S, DevConst K, uint32_t* hist, int n_bins, double z_lo,
                                  double w);

@@ -177,7 +177,7 @@ __device__ __forceinline__ bool try_hit(const DevConst& K, Helix<float>& h, cons
 // a second one is for links that failed.  (A lane each: 1200 and 1249 us for
 // 15000 tracks, as some link of a wave fails at nearly every row.)
 template <int WB, bool kGroup, bool kSearchFirst>
-__device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K, const RowRadii& R, int g0,
+__device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K, const RowTable& R, int g0,
                                                uint32_t total, const LaneGroup& lg) {
   // Tracklets are ordered by (sector, row): give each XCD (blocks are
   // dispatched round-robin over the 8 XCDs) one contiguous chunk, so the
@@ -534,7 +534,7 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
 // and 662; 60 tracks, a wave each, 361 and 381).
 template <bool kSearchFirst>
 __global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g0, uint32_t most) {
-  __shared__ RowRadii R;
+  __shared__ RowTable R;
   const uint32_t total = S.range_cnt[0];
   const uint32_t wide = kWideGroups * most;
   if (kSearchFirst ? total <= wide || total > kGroups * most : total > wide) return;
@@ -546,7 +546,7 @@ __global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g
 template <int WB>
 __global__ void __launch_bounds__(256, WB == 8 ? 1 : 4) k_tracklets(Slot S, DevConst K, int g0,
                                                                              uint32_t few) {
-  __shared__ RowRadii R;
+  __shared__ RowTable R;
   const uint32_t total = S.range_cnt[0];
   if (total <= few) return;
   load_radii(S, R);
