@@ -202,8 +202,7 @@ __device__ __forceinline__ const int32_t* track_hits(const Slot& S, const tpc_tr
 
 // M1, a lane group a track.  Bound like the refit: some 150 steps after one
 // another, each of some 330 instructions that a lone wave issues one by one
-// (2000 tracks 153 us with a lane a track, 142 so on 1024 waves; 15000 tracks
-// 160 either way).
+// (2000 tracks 153 us with a lane a track, 136 so; 15000 tracks 160 either way).
 __global__ void __launch_bounds__(256) k_mg_outer(Slot S, DevConst K, MergeSlot M, MergeConst C) {
   __shared__ RowTable R;
   load_radii(S, R);
@@ -719,7 +718,8 @@ __device__ bool carry_out(const DevConst& K, const RowTable& R, const MergeConst
 // M4: refit of each chain, a lane group a chain.  Bound by the instructions
 // of some 3 x 150 steps after one another.  A lane per track, those that are
 // no heads idle, left 1 to 10 lanes of a wave at work, which then issues at
-// half the rate: 2000 tracks 692 us, now 526; 15000 tracks 702, now 632.
+// half the rate: 2000 tracks 692 us, now 546; 15000 tracks 702, now 655 (526 and
+// 632 on 1024 waves; see kChainWaves).
 __global__ void __launch_bounds__(256) k_mg_chain(Slot S, DevConst K, MergeSlot M, MergeConst C) {
   __shared__ RowTable R;
   load_radii(S, R);

@@ -530,8 +530,8 @@ __device__ __forceinline__ void make_tracklets(const Slot& S, const DevConst& K,
 // kWideGroups of them a wave) a wave has one or two tracklets, and a link that is
 // followed needs no search; with smaller groups some tracklet of a wave
 // searches at nearly every row, and it costs less to let the others wait with
-// their update for it (32 events of 60 tracks 545 us, 480 so; 2000 tracks 708
-// and 662; 60 tracks, a wave each, 361 and 381).
+// their update for it (32 events of 60 tracks 545 us, 480 so; 2000 tracks, then
+// in groups of 8, 708 and 662; 60 tracks, a wave each, 361 and 381).
 template <bool kSearchFirst>
 __global__ void __launch_bounds__(256) k_tracklets_few(Slot S, DevConst K, int g0, uint32_t most) {
   __shared__ RowTable R;
