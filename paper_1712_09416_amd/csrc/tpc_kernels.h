@@ -28,7 +28,7 @@ void launch_neighbours(int wb, int blocks, hipStream_t st, const Slot& S, const 
 // Groups where rows are short (a group of 8 tests one with a read a lane or
 // two, see short_row) are cheaper and the line is later: 7 events of 400 tracks
 // (15000 tracklets, near the most) 1663, 512; 1088, 660; 1092, 550.  32 events of 60
-// with a lane each 1278 alone, 617 with two in flight (1073, 582).
+// with a lane each 1278 alone, 617 with three in flight (1073, 582).
 // One step to either side, 2000 primaries: lanes on 1152 and 896 waves 1231,
 // 481 and 1220, 453; refit on 512 and 320: 1182, 483 and 1188, 455 (but 32
 // events of 60 up to 1150 alone with 320, by where its waves fall).  Groups on
